@@ -38,6 +38,13 @@ constexpr int WTN = BN / WAVES_N;  // 64 cols per wave
 constexpr int TM = WTM / 32, TN = WTN / 32;
 constexpr int LDS_STAGE = (BM + BN) * LDK;  // bf16 elements per stage
 
+// v, hidden from the optimiser, so that what is computed from it stays where it is used (and
+// is not kept in registers across a loop before it).
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 __device__ __forceinline__ bool active_bits(float z) {
   // z > 0 and not NaN: the bits, minus one, as unsigned, are below those of +inf
   return (uint32_t)__float_as_int(z) - 1u < 0x7f800000u;
@@ -270,11 +277,11 @@ template <> struct AccGeo<16> {  // v_mfma_f32_16x16x32_bf16
   static __device__ __forceinline__ uint64_t group(int lane) { return 0xffffull << (lane & 48); }
 };
 
-// With WM_ x WN_ waves, wave (wm, wn) holds the WTM_ x WTN_ block of the tile at
-// (wm*WTM_, wn*WTN_), as TM_ x TN_ MFMA blocks of FM x FM.
-template <int WM_, int WN_, int FM>
+// With WM_ x WN_ waves over a BMT x BN tile, wave (wm, wn) holds the WTM_ x WTN_ block of the
+// tile at (wm*WTM_, wn*WTN_), as TM_ x TN_ MFMA blocks of FM x FM.
+template <int WM_, int WN_, int FM, int BMT = BM>
 struct WaveTile {
-  static constexpr int WTM_ = BM / WM_, WTN_ = BN / WN_, TM_ = WTM_ / FM, TN_ = WTN_ / FM;
+  static constexpr int WTM_ = BMT / WM_, WTN_ = BN / WN_, TM_ = WTM_ / FM, TN_ = WTN_ / FM;
   typedef typename AccGeo<FM>::acc_t acc_t;
   typedef acc_t Acc[TM_][TN_];
 };
@@ -322,15 +329,14 @@ __device__ __forceinline__ void twell_z_lds(const GemmParams& p, typename WaveTi
   }
 }
 
-// The compaction pass over z; cnt_lds holds WN_ x BM ints of block scratch. PK: the packed
+// The compaction pass over z; cnt_lds holds WN_ x BMT ints of block scratch. PK: the packed
 // 32-bit layout (per (row, tile) 32 words: the count in word 0, then column | bf16 << 16).
-template <int WM_, int WN_, int FM, int Tn, bool PK = false>
-__device__ __forceinline__ void twell_compact(const GemmParams& p, typename WaveTile<WM_, WN_, FM>::Acc& acc,
-                                              int wm, int wn, int m0, int n0, int m_eff, int* cnt_lds) {
+template <int WM_, int WN_, int FM, int Tn, bool PK = false, int BMT = BM>
+__device__ __forceinline__ void twell_compact(const GemmParams& p, typename WaveTile<WM_, WN_, FM, BMT>::Acc& acc,
+                                              int wm, int wn, int m0, int n0, int m_eff, int* cnt_lds, int lane) {
   static_assert(Tn == 64 || Tn == 128 || Tn == 256, "TwELL tile width");
-  typedef WaveTile<WM_, WN_, FM> W;
+  typedef WaveTile<WM_, WN_, FM, BMT> W;
   typedef AccGeo<FM> G;
-  const int lane = threadIdx.x & 63;
   const int S = p.tile_slots, NT = p.n_tiles;
   const int wcol0 = n0 + wn * W::WTN_;               // first column of this wave
   constexpr bool spans = Tn > W::WTN_;               // tiles then start on wave boundaries
@@ -356,7 +362,7 @@ __device__ __forceinline__ void twell_compact(const GemmParams& p, typename Wave
             const uint64_t b = ballot(__builtin_amdgcn_classf(acc[i][j][r], 0x380));
             c += __popc((uint32_t)(b >> gsh) & gbits);
           }
-          cnt_lds[wn * BM + wm * W::WTM_ + i * FM + G::row(r, lane)] = c;
+          cnt_lds[wn * BMT + wm * W::WTM_ + i * FM + G::row(r, lane)] = c;
         }
       // The store pass tests z again: keep the compiler from carrying all the ballots of
       // this pass over to it (they would not fit in scalar registers).
@@ -377,7 +383,7 @@ __device__ __forceinline__ void twell_compact(const GemmParams& p, typename Wave
       const uint32_t rowoff = rok ? (uint32_t)grow * (uint32_t)(NT * (PK ? 128 : S * 2)) : kOOB;
       int run = 0;
       if constexpr (spans)
-        for (int w = wn - turn; w < wn; ++w) run += cnt_lds[w * BM + lrow];
+        for (int w = wn - turn; w < wn; ++w) run += cnt_lds[w * BMT + lrow];
 #pragma unroll
       for (int j = 0; j < W::TN_; ++j) {
         if (!spans && (j * FM) % Tn == 0) run = 0;  // wave starts are tile-aligned
@@ -409,15 +415,15 @@ __device__ __forceinline__ void twell_compact(const GemmParams& p, typename Wave
     }
 }
 
-template <int EPI, int WM_, int WN_, int FM, int Tn>
-__device__ __forceinline__ void gemm_epilogue(const GemmParams& p, typename WaveTile<WM_, WN_, FM>::Acc& acc,
+template <int EPI, int WM_, int WN_, int FM, int Tn, int BMT = BM>
+__device__ __forceinline__ void gemm_epilogue(const GemmParams& p, typename WaveTile<WM_, WN_, FM, BMT>::Acc& acc,
                                               int wm, int wn, int m0, int n0, int m_eff, bf16_t* smem) {
-  typedef WaveTile<WM_, WN_, FM> W;
+  typedef WaveTile<WM_, WN_, FM, BMT> W;
   typedef AccGeo<FM> G;
   const int lane = threadIdx.x & 63;
   if constexpr (EPI == EPI_TWELL) {
     twell_z_lds<WM_, WN_, FM>(p, acc, wm, wn, m0, n0, m_eff, smem);
-    twell_compact<WM_, WN_, FM, Tn>(p, acc, wm, wn, m0, n0, m_eff, (int*)smem + BM);
+    twell_compact<WM_, WN_, FM, Tn>(p, acc, wm, wn, m0, n0, m_eff, (int*)smem + BM, lane);
   } else {
 #pragma unroll
     for (int i = 0; i < W::TM_; ++i) {
@@ -548,12 +554,26 @@ __global__ __launch_bounds__(NTHR) void k_gemm_bf16(GemmParams p) {
 // are bank-conflict free; each load instruction writes one contiguous 1 KB. The waves
 // raise their issue priority around MFMA bursts so that the waves still issuing loads or
 // LDS reads do not starve the matrix pipe.
+//
+// Tiles of 128 and of 64 rows (BMT) by the same 256 columns serve the row counts whose 256-row
+// tiles leave CUs idle (see kc_tile_rows): a wave keeps 64 rows, by 64 or 32 columns, and the
+// smaller stages leave room for a ring of three, so that two stages of loads are in flight
+// (a step of these tiles is shorter than the latency of a stage). The k order of every sum
+// is the same at each tile height, so z does not depend on it.
 constexpr int KC_BK = 64;
-constexpr int KC_OPER = BM * KC_BK;              // bf16 elements per operand per stage
-constexpr int KC_STAGE = 2 * KC_OPER;            // A then B
-constexpr int KC_WM = 4, KC_WN = 2, KC_FM = 16;
-constexpr int KC_LOADS = KC_OPER * 2 / 1024 / NWAVES;  // 1 KB load instructions per operand per wave
-static_assert(2 * KC_STAGE * 2 >= (BM + KC_WN * BM) * 4, "TwELL epilogue scratch fits in the stage buffers");
+constexpr int KC_FM = 16;
+constexpr int KC_LOADS = BN * KC_BK * 2 / 1024 / NWAVES;  // 1 KB load instructions per wave and stage of B
+template <int BMT>
+struct KcGeo {
+  static_assert(BMT == 256 || BMT == 128 || BMT == 64, "tile rows");
+  static constexpr int WM = BMT / 64, WN = NWAVES / WM;      // waves along M, N
+  static constexpr int LA = BMT * KC_BK * 2 / 1024 / NWAVES; // 1 KB load instructions per wave and stage of A
+  static constexpr int AOPER = BMT * KC_BK;                  // bf16 elements of A per stage (then B)
+  static constexpr int STAGE = (BMT + BN) * KC_BK;           // bf16 elements per stage
+  static constexpr int NS = BMT == 256 ? 2 : 3;              // stages in the ring
+  typedef WaveTile<WM, WN, KC_FM, BMT> W;
+  static_assert(STAGE * 2 >= WN * BMT * 4, "TwELL epilogue scratch fits in a stage buffer");
+};
 
 __device__ __forceinline__ int kc_swz(int row, int chunk) { return chunk ^ (row & 7); }
 
@@ -605,39 +625,44 @@ typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 
 // Operand staging and MFMA steps of the direct-to-LDS GEMM for one wave: the per-lane
-// source offsets of a 256 x 256 output tile, the loads of one 64-k stage into a stage
+// source offsets of a BMT x 256 output tile, the loads of one 64-k stage into a stage
 // buffer, and the MFMAs over a stage.
-template <int BL>
+template <int BL, int BMT>
 struct KcOps {
   static_assert(BL == LAY_KC || BL == LAY_RC, "B layout");
-  typedef WaveTile<KC_WM, KC_WN, KC_FM> W;
+  typedef KcGeo<BMT> Geo;
+  typedef typename Geo::W W;
   int lane, wave, wm, wn;
   u32x4_t ra, rb;
-  uint32_t offa[KC_LOADS], offb[KC_LOADS];
+  uint32_t offa[Geo::LA], offb[KC_LOADS];
 
   __device__ __forceinline__ explicit KcOps(const GemmParams& p) {
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // wave (wm, wn) = (wave % KC_WM, wave / KC_WM): each SIMD holds one wave of each
+    // wave (wm, wn) = (wave % WM, wave / WM): with 256 rows each SIMD holds one wave of each
     // column of the tile (the TwELL epilogue runs one column of waves at a time)
-    wm = wave % KC_WM;
-    wn = wave / KC_WM;
+    wm = wave % Geo::WM;
+    wn = wave / Geo::WM;
     ra = rsrc_words(p.A, p.a_bytes);
     rb = rsrc_words(p.B, p.b_bytes);
   }
 
-  // Load instruction q of this wave fills rows (wave*KC_LOADS + q)*8 .. +7 of the operand
-  // tile; lane l writes row +l/8 at chunk position l%8, which holds logical chunk
-  // kc_swz(row, l%8).
+  // Load instruction q of this wave's n fills rows (wave*n + q)*8 .. +7 of the operand tile;
+  // lane l writes row +l/8 at chunk position l%8, which holds logical chunk kc_swz(row, l%8).
   __device__ __forceinline__ void setup(const GemmParams& p, int m0, int n0, int m_eff) {
 #pragma unroll
-    for (int q = 0; q < KC_LOADS; ++q) {
-      const int row = (wave * KC_LOADS + q) * 8 + (lane >> 3);
+    for (int q = 0; q < Geo::LA; ++q) {
+      const int row = (wave * Geo::LA + q) * 8 + (lane >> 3);
       const int c = kc_swz(row, lane & 7);
       const int ga = m0 + row;
       const int64_t sa = ga < m_eff ? (p.a_rows ? (int64_t)p.a_rows[ga] : (int64_t)ga) : -1;
       offa[q] = sa >= 0 ? (uint32_t)((sa * p.lda + c * 8) * 2) : kOOB;
+    }
+#pragma unroll
+    for (int q = 0; q < KC_LOADS; ++q) {
       if constexpr (BL == LAY_KC) {
+        const int row = (wave * KC_LOADS + q) * 8 + (lane >> 3);
+        const int c = kc_swz(row, lane & 7);
         const int gb = n0 + row;
         offb[q] = gb < p.N ? (uint32_t)(((int64_t)gb * p.ldb + c * 8) * 2) : kOOB;
       } else {
@@ -650,23 +675,39 @@ struct KcOps {
     }
   }
 
-  // k step kt of the tile into stage buffer st
-  __device__ __forceinline__ void issue(const GemmParams& p, bf16_t* st, int kt) const {
-    const uint32_t soa = (uint32_t)(kt * KC_BK * 2);
-    const uint32_t sob = BL == LAY_KC ? soa : (uint32_t)((int64_t)kt * KC_BK * p.ldb * 2);
+  // LDS address of a stage buffer
+  static __device__ __forceinline__ uint32_t lds_of(const bf16_t* st) {
+    return __builtin_amdgcn_readfirstlane(
+        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const bf16_t*)st);
+  }
+  // Load instructions [q0, q1) of this wave's of A, or of B, for k step kt of the tile into
+  // stage buffer st (1 KB each; A has Geo::LA of them, B KC_LOADS)
+  __device__ __forceinline__ void issue_a(const bf16_t* st, int kt, int q0, int q1) const {
+    const uint32_t so = (uint32_t)(kt * KC_BK * 2);
+#pragma unroll
+    for (int q = q0; q < q1; ++q)
+      if (q < Geo::LA) load_lds16(ra, lds_of(st) + (wave * Geo::LA + q) * 1024, offa[q], so);
+  }
+  __device__ __forceinline__ void issue_b(const GemmParams& p, const bf16_t* st, int kt, int q0, int q1) const {
+    const uint32_t so =
+        BL == LAY_KC ? (uint32_t)(kt * KC_BK * 2) : (uint32_t)((int64_t)kt * KC_BK * p.ldb * 2);
+#pragma unroll
+    for (int q = q0; q < q1; ++q)
+      load_lds16(rb, lds_of(st) + Geo::AOPER * 2 + (wave * KC_LOADS + q) * 1024, offb[q], so);
+  }
+  __device__ __forceinline__ void issue(const GemmParams& p, const bf16_t* st, int kt) const {
 #pragma unroll
     for (int q = 0; q < KC_LOADS; ++q) {
-      bf16_t* da = st + (wave * KC_LOADS + q) * 8 * KC_BK;  // 1 KB per load instruction
-      const uint32_t la = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)da;
-      const uint32_t lb = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)(da + KC_OPER);
-      load_lds16(ra, __builtin_amdgcn_readfirstlane(la), offa[q], soa);
-      load_lds16(rb, __builtin_amdgcn_readfirstlane(lb), offb[q], sob);
+      issue_a(st, kt, q, q + 1);
+      issue_b(p, st, kt, q, q + 1);
     }
   }
 
-  // 16x16x32 operands: lane l supplies row (or column) l%16 at k 8*(l/16) .. +7
-  __device__ __forceinline__ void compute(const bf16_t* As, typename W::Acc& acc) const {
-    const bf16_t* Bs = As + KC_OPER;
+  // 16x16x32 operands: lane l supplies row (or column) l%16 at k 8*(l/16) .. +7. With SPREAD,
+  // between(i) runs before the i-th block row of MFMAs of the first k half.
+  template <bool SPREAD, typename F>
+  __device__ __forceinline__ void compute(const bf16_t* As, typename W::Acc& acc, F between) const {
+    const bf16_t* Bs = As + Geo::AOPER;
     const int arow = wm * W::WTM_ + (lane & 15);
     const int brow = wn * W::WTN_ + (lane & 15);
 #pragma unroll
@@ -703,19 +744,37 @@ struct KcOps {
       }
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int i = 0; i < W::TM_; ++i)
+      for (int i = 0; i < W::TM_; ++i) {
+        if (SPREAD && ks == 0) between(i);
 #pragma unroll
         for (int j = 0; j < W::TN_; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        if constexpr (SPREAD) __builtin_amdgcn_sched_barrier(0);
+      }
       __builtin_amdgcn_s_setprio(0);
     }
   }
 
-  // Stages kt_begin .. kt_end-1 of the tile; stage kt sits in buffer (b0 + kt - kt_begin) & 1
-  // and stage kt_begin has been issued. Each step: this wave's loads of stage kt have
-  // landed and its LDS reads of step kt-1 are complete (vmcnt 0, lgkmcnt 0); after the
-  // barrier the same holds for all waves, so stage kt may be read and the buffer of stage
-  // kt-1 refilled with stage kt+1.
+  // Issues the first stages of K steps [kt_begin, kt_end) (as many as run() expects in
+  // flight), the first one into buffer b0 of the ring.
+  __device__ __forceinline__ void prologue(const GemmParams& p, bf16_t* smem, int b0, int kt_begin, int kt_end) const {
+#pragma unroll
+    for (int i = 0; i < Geo::NS - 1; ++i)
+      if (kt_begin + i < kt_end) issue(p, smem + (b0 + i) % Geo::NS * Geo::STAGE, kt_begin + i);
+  }
+
+  // Stages kt_begin .. kt_end-1 of the tile; stage kt sits in buffer (b0 + kt - kt_begin) % NS
+  // and the first NS - 1 have been issued (prologue). Each step: this wave's loads of stage kt
+  // have landed (with three stages those of stage kt+1, the last ones issued, may still be in
+  // flight; other memory operations after them only make the wait stricter) and its LDS reads
+  // of step kt-1 are complete; after the barrier the same holds for all waves, so stage kt may
+  // be read and the buffer of stage kt-1 refilled with stage kt+NS-1. SPREAD deals the
+  // refill's loads over the first half step's MFMAs, B's (the weights, which come from
+  // further away) before A's, instead of issuing them in one burst that the fragment reads
+  // then queue behind: the up GEMM with the TwELL epilogue at T = 8192, d = 4096, f = 16384
+  // 0.855 -> 0.844 ms with warm weights, at 64-row tiles (T = 509, d = 2048, f = 5632) 28 ->
+  // 26 us; the dense down GEMM (K = 16384) went 0.800 -> 0.832 ms and keeps the burst.
+  template <bool SPREAD>
   __device__ __forceinline__ void run(const GemmParams& p, bf16_t* smem, int b0, int kt_begin, int kt_end,
                                       typename W::Acc& acc) const {
 #pragma unroll
@@ -724,12 +783,27 @@ struct KcOps {
       for (int j = 0; j < W::TN_; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+    constexpr int NS = Geo::NS;
+    static_assert(NS <= 3 && Geo::LA + KC_LOADS < 16, "wait counts below");
+    int ring = b0;  // three stages: the buffer of stage kt
     for (int kt = kt_begin; kt < kt_end; ++kt) {
-      __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) expcnt(7) lgkmcnt(0)
+      if (NS == 3 && kt + 1 < kt_end)
+        __builtin_amdgcn_s_waitcnt(0x0070 | (Geo::LA + KC_LOADS));  // vmcnt(one stage) expcnt(7) lgkmcnt(0)
+      else
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) expcnt(7) lgkmcnt(0)
       __syncthreads();
-      const int bi = (b0 + kt - kt_begin) & 1;
-      if (kt + 1 < kt_end) issue(p, smem + (bi ^ 1) * KC_STAGE, kt + 1);
-      compute(smem + bi * KC_STAGE, acc);
+      const int bi = NS == 2 ? (b0 + kt - kt_begin) & 1 : ring;
+      const int bn = NS == 2 ? bi ^ 1 : (ring == 0 ? NS - 1 : ring - 1);  // the buffer of stage kt-1
+      const bool more = kt + NS - 1 < kt_end;
+      bf16_t* const next = smem + bn * Geo::STAGE;
+      if (!SPREAD && more) issue(p, next, kt + NS - 1);
+      compute<SPREAD>(smem + bi * Geo::STAGE, acc, [&](int i) {
+        if (!more) return;
+        if (i == 0) issue_b(p, next, kt + NS - 1, 0, KC_LOADS);
+        if (i == 1) issue_a(next, kt + NS - 1, 0, 2);
+        if (i == 2) issue_a(next, kt + NS - 1, 2, 4);
+      });
+      if (NS > 2) ring = ring == NS - 1 ? 0 : ring + 1;
     }
   }
 };
@@ -739,17 +813,18 @@ struct KcOps {
 template <int EPI, int BL>
 __device__ __forceinline__ void kc_tile(const GemmParams& p, int tm, int tn, int split, int ks, int m_eff,
                                         bf16_t* smem) {
-  typedef WaveTile<KC_WM, KC_WN, KC_FM> W;
+  typedef KcGeo<BM> Geo;
+  typedef typename Geo::W W;
   typedef AccGeo<KC_FM> G;
   const int m0 = tm * BM, n0 = tn * BN;
   const int nk_all = (int)(p.K / KC_BK);
   const int kt0 = (int)((int64_t)nk_all * split / ks);
   const int kt1 = (int)((int64_t)nk_all * (split + 1) / ks);
-  KcOps<BL> op(p);
+  KcOps<BL, BM> op(p);
   op.setup(p, m0, n0, m_eff);
-  if (kt0 < kt1) op.issue(p, smem, kt0);
+  op.prologue(p, smem, 0, kt0, kt1);
   typename W::Acc acc;
-  op.run(p, smem, 0, kt0, kt1, acc);
+  op.template run<false>(p, smem, 0, kt0, kt1, acc);
   __syncthreads();  // the epilogue reuses the stage buffers
   if (ks > 1) {
     // partial sums of this K range: part[split][row][col], rows in gathered order
@@ -768,15 +843,16 @@ __device__ __forceinline__ void kc_tile(const GemmParams& p, int tm, int tn, int
       }
     return;
   }
-  gemm_epilogue<EPI, KC_WM, KC_WN, KC_FM, 0>(p, acc, op.wm, op.wn, m0, n0, m_eff, smem);
+  gemm_epilogue<EPI, Geo::WM, Geo::WN, KC_FM, 0>(p, acc, op.wm, op.wn, m0, n0, m_eff, smem);
 }
 
 // The TwELL epilogue's optional dense output: h = ReLU(z) in bf16 for every element of the
 // tile (z already in the accumulators; columns past N carry z = -inf and are not stored).
-template <int WM_, int WN_, int FM>
-__device__ __forceinline__ void store_dense_relu(const GemmParams& p, const typename WaveTile<WM_, WN_, FM>::Acc& acc,
-                                                 int wm, int wn, int m0, int n0, int m_eff) {
-  typedef WaveTile<WM_, WN_, FM> W;
+template <int WM_, int WN_, int FM, int BMT>
+__device__ __forceinline__ void store_dense_relu(const GemmParams& p,
+                                                 const typename WaveTile<WM_, WN_, FM, BMT>::Acc& acc, int wm, int wn,
+                                                 int m0, int n0, int m_eff) {
+  typedef WaveTile<WM_, WN_, FM, BMT> W;
   typedef AccGeo<FM> G;
   const int lane = threadIdx.x & 63;
   bf16_t* H = (bf16_t*)p.dense_h;
@@ -796,23 +872,25 @@ __device__ __forceinline__ void store_dense_relu(const GemmParams& p, const type
 }
 
 // TwELL epilogue inputs of one tile held in registers: the shift of row wm*64 + lane and
-// the bias of columns wcol0 + lane and wcol0 + 64 + lane (-inf past N). Lanes fetch the
-// values of their accumulator rows and columns from these with lane permutes.
+// the bias of columns wcol0 + lane and wcol0 + 64 + lane (-inf past N; a wave of fewer
+// columns uses the first ones only). Lanes fetch the values of their accumulator rows and
+// columns from these with lane permutes.
+template <int BMT>
 struct KcTwPre {
+  typedef typename KcGeo<BMT>::W W;
   float sh, b0, b1;
   __device__ __forceinline__ void load(const GemmParams& p, int wm, int wn, int lane, int m0, int n0, int m_eff) {
-    typedef WaveTile<KC_WM, KC_WN, KC_FM> W;
     const int g = m0 + wm * W::WTM_ + lane;
     sh = (p.shift && g < m_eff) ? p.shift[p.s_rows ? p.s_rows[g] : g] : 0.f;
     const int c0 = n0 + wn * W::WTN_ + lane, c1 = c0 + 64;
     b0 = c0 < p.N ? (p.bias ? p.bias[c0] : 0.f) : -__builtin_inff();
-    b1 = c1 < p.N ? (p.bias ? p.bias[c1] : 0.f) : -__builtin_inff();
+    b1 = 0.f;
+    if constexpr (W::WTN_ > 64) b1 = c1 < p.N ? (p.bias ? p.bias[c1] : 0.f) : -__builtin_inff();
   }
   // z = (acc + bias) + shift in place
-  __device__ __forceinline__ void apply(WaveTile<KC_WM, KC_WN, KC_FM>::Acc& acc, int lane) const {
-    typedef WaveTile<KC_WM, KC_WN, KC_FM> W;
+  __device__ __forceinline__ void apply(typename W::Acc& acc, int lane) const {
     typedef AccGeo<KC_FM> G;
-    static_assert(W::WTM_ == 64 && W::WTN_ == 128, "one shift and two bias values per lane");
+    static_assert(W::WTM_ == 64 && W::WTN_ <= 128, "one shift and two bias values per lane");
     float shv[W::TM_][G::R];
 #pragma unroll
     for (int i = 0; i < W::TM_; ++i)
@@ -837,12 +915,13 @@ struct KcTwPre {
 // tile's epilogue runs, the first stage of the block's next tile is already loading
 // (into the stage buffer the epilogue does not use), and for the TwELL epilogue so are
 // the next tile's bias and shift values.
-template <int EPI, int Tn, int BL>
+template <int EPI, int Tn, int BL, int BMT>
 __global__ __launch_bounds__(NTHR) void k_gemm_kc(GemmParams p) {
-  __shared__ __attribute__((aligned(1024))) bf16_t smem[2 * KC_STAGE];
+  typedef KcGeo<BMT> Geo;
+  typedef typename Geo::W W;
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[Geo::NS * Geo::STAGE];
   if (blockIdx.x == 0) zero_first(p);
-  typedef WaveTile<KC_WM, KC_WN, KC_FM> W;
-  const int tiles_m = (int)cdiv(p.M, BM), tiles_n = (int)cdiv(p.N, BN);
+  const int tiles_m = (int)cdiv(p.M, BMT), tiles_n = (int)cdiv(p.N, BN);
   const int nt = tiles_m * tiles_n;
   const int m_eff = p.m_count ? min(*p.m_count, p.count_cap) : p.M;
   const int nk = (int)(p.K / KC_BK);
@@ -850,46 +929,51 @@ __global__ __launch_bounds__(NTHR) void k_gemm_kc(GemmParams p) {
   auto next_live = [&](int v, int& tm, int& tn) {
     for (; v < nt; v += gridDim.x) {
       tile_coords(v, tiles_m, tiles_n, tm, tn, p.tile_order);
-      if (tm * BM < m_eff) break;
+      if (tm * BMT < m_eff) break;
     }
     return v;
   };
   int tm, tn;
   int v = next_live(blockIdx.x, tm, tn);
   if (v >= nt) return;
-  KcOps<BL> op(p);
-  op.setup(p, tm * BM, tn * BN, m_eff);
-  if (nk > 0) op.issue(p, smem, 0);
+  KcOps<BL, BMT> op(p);
+  op.setup(p, tm * BMT, tn * BN, m_eff);
+  op.prologue(p, smem, 0, 0, nk);
   constexpr bool TW = EPI == EPI_TWELL || EPI == EPI_TWELL_P32;
-  KcTwPre pre;
-  if constexpr (TW) pre.load(p, op.wm, op.wn, op.lane, tm * BM, tn * BN, m_eff);
+  KcTwPre<BMT> pre;
+  if constexpr (TW) pre.load(p, op.wm, op.wn, op.lane, tm * BMT, tn * BN, m_eff);
   int b0 = 0;  // stage buffer of the tile's first k step
   for (;;) {
     typename W::Acc acc;
-    op.run(p, smem, b0, 0, nk, acc);
-    const int bl = (b0 + nk - 1) & 1;  // buffer of the last k step: the epilogue's scratch
-    const int m0 = tm * BM, n0 = tn * BN;
+    op.template run<TW>(p, smem, b0, 0, nk, acc);
+    // buffer of the last k step: the epilogue's scratch
+    const int bl = Geo::NS == 2 ? (b0 + nk - 1) & 1 : (b0 + nk + Geo::NS - 1) % Geo::NS;
+    const int m0 = tm * BMT, n0 = tn * BN;
     int tm2 = 0, tn2 = 0;
     const int v2 = next_live(v + gridDim.x, tm2, tn2);
-    KcTwPre pre2;
+    KcTwPre<BMT> pre2;
     if constexpr (TW) pre.settle();
     if (v2 < nt) {
       // before the stage issue, so that no wait of the compiler's (a gathered shift row)
-      // waits for the stage; the other buffer was last read in step nk-2, which every wave
-      // finished before the barrier of step nk-1
-      if constexpr (TW) pre2.load(p, op.wm, op.wn, op.lane, tm2 * BM, tn2 * BN, m_eff);
-      op.setup(p, tm2 * BM, tn2 * BN, m_eff);
-      if (nk > 0) op.issue(p, smem + (bl ^ 1) * KC_STAGE, 0);
+      // waits for the stage; the other buffers were last read in steps before nk-1, which
+      // every wave finished before the barrier of step nk-1
+      if constexpr (TW) pre2.load(p, op.wm, op.wn, op.lane, tm2 * BMT, tn2 * BN, m_eff);
+      op.setup(p, tm2 * BMT, tn2 * BN, m_eff);
+      op.prologue(p, smem, (bl + 1) % Geo::NS, 0, nk);
     }
     __syncthreads();  // every wave is done reading buffer bl
-    bf16_t* scratch = smem + bl * KC_STAGE;
+    bf16_t* scratch = smem + bl * Geo::STAGE;
     if constexpr (EPI == EPI_TWELL || EPI == EPI_TWELL_P32) {
-      pre.apply(acc, op.lane);
-      if (p.dense_h) store_dense_relu<KC_WM, KC_WN, KC_FM>(p, acc, op.wm, op.wn, m0, n0, m_eff);
-      twell_compact<KC_WM, KC_WN, KC_FM, Tn, EPI == EPI_TWELL_P32>(p, acc, op.wm, op.wn, m0, n0, m_eff,
-                                                                    (int*)scratch);
+      // row-contiguous B takes more registers in the K loop: with the epilogue's per-lane
+      // constants kept across it the 256-row tile spilled its load offsets, and each reload
+      // waited for the loads before it (T = 8192, d = 4096, f = 14336: 0.86 -> 0.79 ms)
+      const int lane = BL == LAY_RC ? opaque(op.lane) : op.lane;
+      pre.apply(acc, lane);
+      if (p.dense_h) store_dense_relu<Geo::WM, Geo::WN, KC_FM, BMT>(p, acc, op.wm, op.wn, m0, n0, m_eff);
+      twell_compact<Geo::WM, Geo::WN, KC_FM, Tn, EPI == EPI_TWELL_P32, BMT>(p, acc, op.wm, op.wn, m0, n0, m_eff,
+                                                                             (int*)scratch, lane);
     } else {
-      gemm_epilogue<EPI, KC_WM, KC_WN, KC_FM, Tn>(p, acc, op.wm, op.wn, m0, n0, m_eff, scratch);
+      gemm_epilogue<EPI, Geo::WM, Geo::WN, KC_FM, Tn, BMT>(p, acc, op.wm, op.wn, m0, n0, m_eff, scratch);
     }
     if (v2 >= nt) break;
     // the first barrier of the next tile's K loop orders this epilogue's scratch use before
@@ -897,7 +981,7 @@ __global__ __launch_bounds__(NTHR) void k_gemm_kc(GemmParams p) {
     v = v2;
     tm = tm2;
     tn = tn2;
-    b0 = bl ^ 1;
+    b0 = (bl + 1) % Geo::NS;
     if constexpr (TW) pre = pre2;
   }
 }
@@ -906,7 +990,7 @@ __global__ __launch_bounds__(NTHR) void k_gemm_kc(GemmParams p) {
 // the grid does not scale with a row capacity that the count may leave mostly empty.
 template <int EPI, int BL>
 __global__ __launch_bounds__(NTHR) void k_gemm_kc_split(GemmParams p) {
-  __shared__ __attribute__((aligned(1024))) bf16_t smem[2 * KC_STAGE];
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[KcGeo<BM>::NS * KcGeo<BM>::STAGE];
   const int m_eff = p.m_count ? min(*p.m_count, p.count_cap) : p.M;
   const int tiles_n = (int)cdiv(p.N, BN);
   const int ks = splitk_count(p.ksplit, p.part_rows, m_eff, p.N, (int)(p.K / KC_BK));
@@ -1203,14 +1287,47 @@ int device_cus() {
   return n;
 }
 
-template <int EPI, int Tn = 0, int BL = LAY_KC>
-hipError_t launch_kc(const GemmParams& p, hipStream_t s) {
-  const int64_t tiles = cdiv(p.M, BM) * cdiv(p.N, BN);
+// Rows per output tile of the TwELL GEMM: the height whose rounds of one tile per CU cost
+// least, a round of 128-row tiles at 0.62 and of 64-row tiles at 0.47 of a round of 256-row
+// ones (measured at K = 1024, 2048 and 4096 with idle CUs left). A 256-row tile does the most
+// work per byte loaded and wins wherever its tiles fill the CUs; up to about a thousand rows
+// they do not: T = 509, d = 2048, f = 5632 (44, 88 or 176 tiles) 57, 35 and 26 us, T = 300,
+// d = 4096, f = 16384 (128, 192 or 320) 99, 61 and 90 us, T = 1024 (256, 512 or 1024) 115, 141
+// and 200 us.
+int kc_tile_rows(const GemmParams& p) {
+  constexpr int rows[] = {256, 128, 64}, cost[] = {100, 62, 47};
+  int best = BM;
+  int64_t least = INT64_MAX;
+  for (int i = 0; i < 3; ++i) {
+    const int64_t c = cdiv(cdiv(p.M, rows[i]) * cdiv(p.N, BN), device_cus()) * cost[i];
+    if (c < least) {
+      least = c;
+      best = rows[i];
+    }
+  }
+  return best;
+}
+
+template <int EPI, int Tn, int BL, int BMT>
+hipError_t launch_kc_rows(const GemmParams& p, hipStream_t s) {
+  const int64_t tiles = cdiv(p.M, BMT) * cdiv(p.N, BN);
   if (tiles == 0) return hipSuccess;
   // one persistent block per CU (the stage buffers allow one per CU)
   const unsigned grid = (unsigned)std::min<int64_t>(tiles, device_cus());
-  hipLaunchKernelGGL((k_gemm_kc<EPI, Tn, BL>), dim3(grid), dim3(NTHR), 0, s, p);
+  hipLaunchKernelGGL((k_gemm_kc<EPI, Tn, BL, BMT>), dim3(grid), dim3(NTHR), 0, s, p);
   return hipGetLastError();
+}
+
+template <int EPI, int Tn = 0, int BL = LAY_KC>
+hipError_t launch_kc(const GemmParams& p, hipStream_t s) {
+  if constexpr (EPI == EPI_TWELL || EPI == EPI_TWELL_P32) {
+    switch (kc_tile_rows(p)) {
+      case 64: return launch_kc_rows<EPI, Tn, BL, 64>(p, s);
+      case 128: return launch_kc_rows<EPI, Tn, BL, 128>(p, s);
+      default: break;
+    }
+  }
+  return launch_kc_rows<EPI, Tn, BL, BM>(p, s);
 }
 
 // Split-K launch: the GEMM over (tile, split) blocks, then the partial-sum reduction. The

@@ -182,6 +182,38 @@ def test_fused_twell_equals_pack_of_same_mainloop(T, f, Tn, S, use_wupt):
     assert rel_l2(to_f64(Y)[rows], Yref) <= 2e-2
 
 
+@pytest.mark.parametrize("use_wupt", [False, True])
+@pytest.mark.parametrize("T,d,f,Tn,S,layout", [
+    (257, 64, 320, 256, 32, 0), (321, 128, 1984, 256, 31, 1), (259, 192, 1088, 64, 16, 0),   # 64-row tiles
+    (530, 64, 14336, 128, 16, 0), (530, 256, 14336, 256, 32, 0),                            # 64 rows, two rounds
+    (300, 64, 16384, 256, 32, 0), (1000, 192, 5632, 128, 16, 0), (900, 128, 5632, 256, 31, 1),  # 128 rows
+    (3000, 192, 5632, 64, 8, 0)])                                                           # 128 rows, three rounds
+def test_fused_twell_tile_heights(T, d, f, Tn, S, layout, use_wupt):
+    """The TwELL GEMM picks 64-, 128- or 256-row tiles by the number of tiles: at every height
+    (one to four K steps around the ring of stages, ragged T and f, one and several tiles per
+    block, both weight layouts, planes and packed words) the TwELL is the oracle's extraction
+    of the same main loop's float32 pre-activations, bit for bit."""
+    w = wl.make_ffn("tile heights", "bf16", T, d, f, seed=T + d, sparsity=0.98, tile_cols=Tn, tile_slots=S,
+                    ell_width=512)
+    w.cfg["layout"] = layout
+    _, bufs, _, cfg = run_forward(w, use_wupt=use_wupt)
+    X, Wu = dev(w.X), dev(w.W_up)
+    Z = torch.empty((T, f), dtype=torch.float32, device="cuda")
+    b.sfl_up_projection(b.ffn_args(X, Wu, dev(w.W_down), cfg, shift_t=dev(w.shift_t),
+                                   W_upT=transposed(Wu) if use_wupt else None), Z)
+    torch.cuda.synchronize()
+    tw = twell.extract_twell(Z.cpu().numpy(), Tn, S, "bf16")
+    if layout:
+        want = twell.pack32(tw)
+        got = host_bits(bufs["val"])[:want.size].view(np.uint32).reshape(want.shape)
+        word = np.arange(32)[None, None, :]
+        used = (word <= np.minimum(tw.cnt, S)[:, :, None]).reshape(want.shape)  # the count and the kept entries
+        np.testing.assert_array_equal(np.where(used, got, 0), want)
+        np.testing.assert_array_equal(host_bits(bufs["row_nnz"])[:T], tw.cnt.sum(axis=1))
+    else:
+        assert_twell_equal(twell_views(bufs, T, f, cfg), tw, twell.classify(tw, cfg.ell_width))
+
+
 @pytest.mark.parametrize("Tn,S,packed", [(256, 32, False), (128, 16, False), (64, 8, False), (256, 31, True)])
 def test_rebuilt_dense_backup_rows_bit_exact(Tn, S, packed):
     """Above 256 tokens the dense-backup rows whose tiles all kept their values are rebuilt
