@@ -190,7 +190,7 @@ int64_t align_rows(int64_t r) { return (r + 255) / 256 * 256; }
 
 // Up to 64 tokens the gather's first block builds the dense-backup row list, else the list
 // kernel (which then also adds the classification blocks' statistics).
-bool list_by_gather(const sfl_ffn_args_t& a) { return a.T <= 64 && packed_gather(a) && !dense_candidate(a); }
+bool list_by_gather(const sfl_ffn_args_t& a) { return a.T <= 64 && !dense_candidate(a); }
 
 FwdPlan plan_forward(const sfl_ffn_args_t& a, void* ws) {
   Carve c(ws);
@@ -204,7 +204,7 @@ FwdPlan plan_forward(const sfl_ffn_args_t& a, void* ws) {
   }
   if (a.gated && !a.W_up_packed && !a.W_upT) p.WupT = c.take((size_t)a.f * a.d * elem_size(a.dtype));
   if (packed_gather(a) && !a.W_down_packed) p.WdP = c.take((size_t)a.f * a.d * 2);
-  if (packed_gather(a)) p.order = (int32_t*)c.take((size_t)a.T * 4);
+  if (a.dtype == SFL_BF16) p.order = (int32_t*)c.take((size_t)a.T * 4);
   if (a.gated && !a.W_up_packed) p.WuP = c.take((size_t)a.f * a.d * 2);
   if (a.gated) {
     const int64_t K = std::max<int64_t>(a.cfg.ell_width, 1);
@@ -614,6 +614,12 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
                                           a->cfg.tile_slots, tw.val, tw.idx, tw.cnt, s, packed_layout(a->cfg)));
         }
       } else {
+        if (a->dtype == SFL_F32) {  // the fp32 GEMM clears them itself
+          g.zero_stats = a->stats;
+          g.zero = counters;
+          g.n_zero = counters ? plan.n_zero : 0;
+          cleared = true;
+        }
         SFL_HIP(clear_first());
         SFL_HIP(run_gemm(a->dtype, LAY_KC, blay, EPI_F32, g, s));
         if (row_classify && ((uintptr_t)plan.Z & 15) == 0) {
@@ -641,7 +647,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   // rows the gather's first block builds it, with the token order a second workgroup of
   // the order kernel, else its own kernel
   OvfList late_list;
-  const bool list_by_order = !list_by_gather(*a) && packed_gather(*a) && nnz_token_order(*a);
+  const bool list_by_order = !list_by_gather(*a) && bf && nnz_token_order(*a);
   const int n_cls_part = cls_part ? (int)classify_grid(T, f, a->cfg.tile_cols) : 0;
   if (list_by_gather(*a) || list_by_order) {
     late_list.rows = tw.ovf_rows;
@@ -675,7 +681,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   }
   // 3. sparse down projection of the ELL rows
   const void* WupT = a->W_upT;  // gated: W_up^T, given or built in the workspace when needed
-  if (packed_gather(*a)) {
+  if (bf) {
     const int32_t* order = nullptr;
     if (nnz_token_order(*a)) {
       // with a second workgroup building the dense-backup row list
@@ -683,7 +689,9 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
                                list_by_order ? &late_list : nullptr, cls_part, n_cls_part));
       order = plan.order;
     }
-    const void* WdP = a->W_down_packed;
+    // widths that do not deal out evenly over the XCDs read W_down as it is
+    const bool row_major = !packed_gather(*a);
+    const void* WdP = row_major ? a->W_down : a->W_down_packed;
     if (!WdP) {
       SFL_HIP(launch_pack_down(a->W_down, plan.WdP, f, d, s));
       WdP = plan.WdP;
@@ -719,10 +727,10 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
     SFL_HIP(launch_gather_down_packed(T, d, f, a->cfg.ell_width, hv, tw.ell_idx, tw.row_nnz, tw.row_ovf, WdP, a->Y,
                                       s, 0, 0, nullptr, order, plan.dense_flags ? plan.dense_flags + 1 : nullptr,
                                       form_h ? plan.part_u : nullptr, form_h ? a->stats : nullptr,
-                                      list_by_order ? OvfList{} : late_list));
+                                      list_by_order ? OvfList{} : late_list, row_major));
   } else {
-    SFL_HIP(launch_gather_down(vb, T, d, a->cfg.ell_width, tw.ell_val, tw.ell_idx, tw.row_nnz, tw.row_ovf,
-                               a->W_down, a->Y, s));
+    SFL_HIP(launch_gather_down(T, d, a->cfg.ell_width, (const float*)tw.ell_val, tw.ell_idx, tw.row_nnz, tw.row_ovf,
+                               (const float*)a->W_down, (float*)a->Y, s, late_list));
   }
   ev.record(3, s);
   // 4. dense-backup rows (Alg. 3, dense part), count on device: the dense ReLU rows are
@@ -782,7 +790,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
     } else {
       if (!a->gated && !rebuild) {
         g.l1_stats = a->stats;
-        l1_in_gemm = few_rows_tile_epilogue(g, blay);
+        l1_in_gemm = !bf || few_rows_tile_epilogue(g, blay);
         if (!l1_in_gemm) g.l1_stats = nullptr;
       }
       SFL_HIP(run_gemm(a->dtype, LAY_KC, blay, EPI_ACT_RELU, g, s));

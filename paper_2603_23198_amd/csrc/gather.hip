@@ -1,12 +1,12 @@
 // Sparse down projections from the compact ELL rows of the hybrid format.
 //
 // Non-gated (Alg. 3, sparse part): y[t, :] = sum_e v[t, e] * W_down[n[t, e], :].
-//  * k_gather_down (any dtype, any d): (d-slice of 128 columns) x (block of tokens); a
-//    wave owns one token at a time and walks its ELL entries in order, reading one
-//    256-byte W_down row segment per entry.
-//  * k_gather_down_b16 (bf16, d % 512 == 0): over a slice-major copy of W_down, each XCD
-//    walking its own 64-column slices so that one 2 MiB slice stays in its L2 while every
-//    token streams through it (see below). A work item is (slice, token), the 8 lane
+//  * k_gather_down (fp32, any d): (d-slice of 128 columns) x (block of tokens); a wave owns
+//    one token at a time and walks its ELL entries in order, reading one 512-byte W_down row
+//    segment per entry.
+//  * k_gather_down_b16 (bf16): over a slice-major copy of W_down (d % 512 == 0; other widths
+//    over W_down itself), each XCD walking its own 64-column slices so that one 2 MiB slice
+//    stays in its L2 while every token streams through it (see below). A work item is (slice, token), the 8 lane
 //    groups of the wave splitting the token's entries and folding their sums, or, for
 //    large batches of short rows, (slice, 8 tokens), one token per lane group.
 //
@@ -28,33 +28,39 @@ namespace sfl {
 namespace {
 
 constexpr int SLICE = 128;  // columns per slice (64 lanes x 2)
-constexpr int TOK_PER_WG = 32;
 
-template <typename V> struct Pair;
-template <> struct Pair<bf16_t> {
-  typedef uint32_t raw;
-  static __device__ __forceinline__ raw load(const bf16_t* p) { return *(const uint32_t*)p; }
-  static __device__ __forceinline__ float lo(raw w) { return bf16lo(w); }
-  static __device__ __forceinline__ float hi(raw w) { return bf16hi(w); }
-  static __device__ __forceinline__ void store(bf16_t* p, float a, float b) {
-    *(uint32_t*)p = (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
+// The ascending dense-backup row list of a batch of at most 64 rows (one wave; in place of
+// the list kernel): lane t takes row t, the ballot of the flags gives each flagged row its
+// position; the count, and the statistics' row count and capacity flag, from lane 0.
+__device__ __forceinline__ void ovf_list_small(int64_t T, const OvfList& ol, const uint8_t* __restrict__ row_ovf) {
+  const int l = threadIdx.x & 63;
+  const bool flag = l < T && row_ovf[l];
+  const uint64_t m = ballot(flag);
+  const int pos = mbcnt(m);
+  if (flag && pos < ol.cap) ol.rows[pos] = l;
+  if (l == 0) {
+    const int n = __popcll(m);
+    *ol.n = n;
+    if (ol.stats) {
+      ol.stats->n_ovf_rows = n;
+      ol.stats->capacity_exceeded = n > ol.cap ? 1 : 0;
+    }
   }
-};
-template <> struct Pair<float> {
-  typedef float2 raw;
-  static __device__ __forceinline__ raw load(const float* p) { return *(const float2*)p; }
-  static __device__ __forceinline__ float lo(raw w) { return w.x; }
-  static __device__ __forceinline__ float hi(raw w) { return w.y; }
-  static __device__ __forceinline__ void store(float* p, float a, float b) { *(float2*)p = make_float2(a, b); }
-};
+}
 
-template <typename V>
-__global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K, const V* __restrict__ ell_val,
+// Workgroups of tpw tokens (launch_gather_down sizes them); a wave's tokens are wave, wave +
+// 4, .... A token's count, flag and first 64 entries are loaded together (entries past the
+// row's count are read, within the row's K, and not used), so that a row of up to 64 entries
+// waits for memory twice: its entries, then W. ODD: d is odd, the last lane of a row holds
+// one column.
+template <bool ODD>
+__global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K, const float* __restrict__ ell_val,
                                                      const uint16_t* __restrict__ ell_idx,
                                                      const int32_t* __restrict__ row_nnz,
-                                                     const uint8_t* __restrict__ row_ovf, const V* __restrict__ W,
-                                                     V* __restrict__ Y, int n_slices, int n_tb) {
-  typedef Pair<V> P;
+                                                     const uint8_t* __restrict__ row_ovf, const float* __restrict__ W,
+                                                     float* __restrict__ Y, int n_slices, int n_tb, int tpw,
+                                                     OvfList ol) {
+  if (ol.rows && blockIdx.x == 0 && threadIdx.x < 64) ovf_list_small(T, ol, row_ovf);
   const int g = blockIdx.x;
   int slice, tb;
   if ((n_slices & 7) == 0) {
@@ -70,44 +76,74 @@ __global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K
   const int wave = threadIdx.x >> 6;
   const int64_t col = (int64_t)slice * SLICE + 2 * l;
   const bool col_ok = col < d;
-  for (int tt = wave; tt < TOK_PER_WG; tt += 4) {
-    const int64_t t = (int64_t)tb * TOK_PER_WG + tt;
+  const bool two = !ODD || col + 1 < d;
+  auto load_w = [&](int64_t n) -> float2 {
+    if (!col_ok) return make_float2(0.f, 0.f);
+    if (!two) return make_float2(W[n * d + col], 0.f);
+    return *(const float2*)(W + n * d + col);
+  };
+  for (int tt = wave; tt < tpw; tt += 4) {
+    const int64_t t = (int64_t)tb * tpw + tt;
     if (t >= T) break;
-    if (__builtin_amdgcn_readfirstlane(row_ovf[t])) continue;
-    const int nnz = __builtin_amdgcn_readfirstlane(row_nnz[t]);
-    float a0 = 0.f, a1 = 0.f;
-    const V* ev = ell_val + t * (int64_t)K;
+    const float* ev = ell_val + t * (int64_t)K;
     const uint16_t* ei = ell_idx + t * (int64_t)K;
+    const uint8_t ovf = row_ovf[t];
+    const int cnt_t = row_nnz[t];
+    const int l0 = min(l, max(K - 1, 0));
+    int n_l = K > 0 ? (int)ei[l0] : 0;
+    float v_l = K > 0 ? ev[l0] : 0.f;
+    if (__builtin_amdgcn_readfirstlane((int)ovf)) continue;
+    const int nnz = __builtin_amdgcn_readfirstlane(cnt_t);
+    float a0 = 0.f, a1 = 0.f;
     for (int e0 = 0; e0 < nnz; e0 += 64) {
       const int e = e0 + l;
-      const int n_l = e < nnz ? (int)ei[e] : 0;
-      const float v_l = e < nnz ? VT<V>::load(ev, e) : 0.f;
+      if (e0 > 0) {
+        n_l = e < nnz ? (int)ei[e] : 0;
+        v_l = e < nnz ? ev[e] : 0.f;
+      }
       const int cnt = min(64, nnz - e0);
       int q = 0;
       for (; q + 8 <= cnt; q += 8) {
-        typename P::raw w[8];
+        float2 w[8];
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const int64_t n = readlane_i(n_l, q + u);
           v[u] = readlane_f(v_l, q + u);
-          w[u] = col_ok ? P::load(W + n * d + col) : typename P::raw{};
+          w[u] = load_w(readlane_i(n_l, q + u));
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          a0 = fmaf(v[u], P::lo(w[u]), a0);
-          a1 = fmaf(v[u], P::hi(w[u]), a1);
+          a0 = fmaf(v[u], w[u].x, a0);
+          a1 = fmaf(v[u], w[u].y, a1);
         }
       }
-      for (; q < cnt; ++q) {
-        const int64_t n = readlane_i(n_l, q);
-        const float v = readlane_f(v_l, q);
-        const typename P::raw w = col_ok ? P::load(W + n * d + col) : typename P::raw{};
-        a0 = fmaf(v, P::lo(w), a0);
-        a1 = fmaf(v, P::hi(w), a1);
+      if (q < cnt) {
+        // the last entries of the row, up to 8: absent ones re-read the last and add nothing
+        float2 w[8];
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int qq = min(q + u, cnt - 1);
+          v[u] = readlane_f(v_l, qq);
+          w[u] = load_w(readlane_i(n_l, qq));
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if (q + u < cnt) {
+            a0 = fmaf(v[u], w[u].x, a0);
+            a1 = fmaf(v[u], w[u].y, a1);
+          }
+        }
       }
     }
-    if (col_ok) P::store(Y + t * d + col, a0, a1);
+    if (col_ok) {
+      if constexpr (ODD) {
+        Y[t * d + col] = a0;
+        if (two) Y[t * d + col + 1] = a1;
+      } else {
+        *(float2*)(Y + t * d + col) = make_float2(a0, a1);
+      }
+    }
   }
 }
 
@@ -216,13 +252,13 @@ __device__ __forceinline__ void fold_groups(float (&acc)[8]) {
 }
 
 // One token's slice: entries er[0..nnz) in LDS, W row segments read through the buffer
-// descriptor at byte offset idx * 2 * SLICE + col_b; on return the lanes of group 0 hold
+// descriptor at byte offset idx * (row stride) + col_b; on return the lanes of group 0 hold
 // the sums of their 8 columns.
-template <int U>
+template <int U, bool RM>
 __device__ __forceinline__ void slice_token(const uint32_t* er, int nnz, __amdgpu_buffer_rsrc_t wr, uint32_t col_b,
-                                            int grp, float (&acc)[8]) {
+                                            uint32_t row_stride, int grp, float (&acc)[8]) {
   static_assert(U % 2 == 0, "entries are consumed in pairs");
-  constexpr uint32_t row_b = SLICE2 * 2;
+  const uint32_t row_b = RM ? row_stride : SLICE2 * 2;
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = 0.f;
   for (int q = 0; q < nnz; q += NGRP * U) {
@@ -232,7 +268,7 @@ __device__ __forceinline__ void slice_token(const uint32_t* er, int nnz, __amdgp
     for (int u = 0; u < U; ++u) {
       const int e = q + u * NGRP + grp;
       x[u] = e < nnz ? er[e] : 0u;  // an absent entry has value 0 (and its load reads 0)
-      const uint32_t off = e < nnz ? (x[u] & 0xffffu) * row_b + col_b : 0x80000000u;
+      const uint32_t off = e < nnz ? __umul24(x[u] & 0xffffu, row_b) + col_b : 0x80000000u;
       w[u] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(wr, (int)off, 0, 0));
     }
     // two entries at a time: (v_a, v_b) . (w_a[c], w_b[c]) with one bf16 dot2 per column
@@ -310,26 +346,15 @@ __device__ __forceinline__ void store_slice(bf16_t* Y, float* Yf, int64_t o, flo
   }
 }
 
-// The ascending dense-backup row list of a batch of at most 64 rows (one wave; in place of
-// the list kernel): lane t takes row t, the ballot of the flags gives each flagged row its
-// position; the count, and the statistics' row count and capacity flag, from lane 0.
-__device__ __forceinline__ void ovf_list_small(int64_t T, const OvfList& ol, const uint8_t* __restrict__ row_ovf) {
-  const int l = threadIdx.x & 63;
-  const bool flag = l < T && row_ovf[l];
-  const uint64_t m = ballot(flag);
-  const int pos = mbcnt(m);
-  if (flag && pos < ol.cap) ol.rows[pos] = l;
-  if (l == 0) {
-    const int n = __popcll(m);
-    *ol.n = n;
-    if (ol.stats) {
-      ol.stats->n_ovf_rows = n;
-      ol.stats->capacity_exceeded = n > ol.cap ? 1 : 0;
-    }
-  }
-}
-
-template <int VK, int OUT, int U, bool TG = false>
+// RM: W is the row-major W_down [f][d] itself (d any multiple of 64), else the slice-major copy
+// (d a multiple of 512). Where the slices do not deal out evenly over the XCDs, every XCD
+// walks n_slices / 8 of its own and the n_slices % 8 left over are dealt over the XCDs anew
+// for each token block, so that all XCDs get the same work (d = 1600: 25 slices; the last
+// one on XCD 0 alone would leave the others idle for a fourth of the time). Against a wave per
+// (token, 128 columns) reading W_down rows in token order, which served these widths before:
+// forward at d = 1600, f = 6400, 99 %: T = 8000 397 -> 290 us, T = 20 61 -> 23 us; d = 768,
+// f = 3072, T = 8000 132 -> 110 us.
+template <int VK, int OUT, int U, bool TG = false, bool RM = false>
 __global__ __launch_bounds__(GATHER_WAVES * 64) void k_gather_down_b16(
     int64_t T, int64_t d, int64_t f, int K, const void* __restrict__ ell_val, const uint16_t* __restrict__ ell_idx,
     const int32_t* __restrict__ row_nnz, const uint8_t* __restrict__ row_ovf, const bf16_t* __restrict__ W,
@@ -341,7 +366,7 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void k_gather_down_b16(
   constexpr int EW = VK + 1;         // words per staged entry
   // bf16 entries of the token-group walk: offsets [tpw][KS] and values [tpw][KV] (above)
   constexpr bool SPLIT = VK == 0 && TG;
-  constexpr uint32_t row_b = SLICE2 * 2;
+  const uint32_t row_b = RM ? (uint32_t)d * 2u : SLICE2 * 2u;  // bytes from one W row (segment) to the next
   // token groups read 8 tokens' entries at once: an odd stride puts them in different banks
   const int KS = TG ? K + 1 : K;
   const int KV = SPLIT ? tg_value_stride(K) : 0;
@@ -458,7 +483,13 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void k_gather_down_b16(
   // work items (slice of this XCD, token) in slice-major order, dealt round-robin to the
   // waves: the workgroup walks the slices in order, and a small block (decode) still
   // keeps every wave busy
-  const int nsl = (n_slices - xcd + 7) / 8;
+  const int full = n_slices >> 3, rem = n_slices & 7;
+  const int extra = RM ? (xcd - (int)(blockIdx.x >> 3) % 8 * rem) & 7 : 0;  // of the slices left over, if < rem
+  const int nsl = RM ? full + (extra < rem ? 1 : 0) : (n_slices - xcd + 7) / 8;
+  auto slice_of = [&](int k) -> int { return RM && k == full ? 8 * full + extra : xcd + 8 * k; };
+  auto slice_byte = [&](int slice) -> uint32_t {
+    return RM ? (uint32_t)slice * (SLICE2 * 2) : (uint32_t)(slice * f * SLICE2 * 2);
+  };
   if constexpr (TG) {
     static_assert(VK == 1 || U % 2 == 0, "bf16 entries are consumed in pairs");
     // Short rows: a work item is (slice, NGRP tokens), lane group g walking token g's
@@ -466,7 +497,7 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void k_gather_down_b16(
     // to the longest of its tokens' rows (absent entries load nothing and add 0).
     const int n_grp = (tpw + NGRP - 1) / NGRP;
     for (int it = wave; it < nsl * n_grp; it += GATHER_WAVES) {
-      const int slice = xcd + 8 * (it / n_grp);
+      const int slice = slice_of(it / n_grp);
       const int i = (it % n_grp) * NGRP + grp;
       const int c = i < tpw ? cnt_s[i] : -1;
       int cmax = c, cmin = c;
@@ -478,7 +509,7 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void k_gather_down_b16(
       cmax = __builtin_amdgcn_readfirstlane(cmax);
       cmin = __builtin_amdgcn_readfirstlane(cmin);
       if (cmax < 0) continue;
-      const uint32_t col_b = (uint32_t)(slice * f * SLICE2 * 2) + (uint32_t)sub * 16u;
+      const uint32_t col_b = slice_byte(slice) + (uint32_t)sub * 16u;
       const uint32_t* er = ent + (size_t)(i < tpw ? i : 0) * KS * EW;
       const bf16_t* ev = val_s + (size_t)(i < tpw ? i : 0) * KV;
       float acc[8];
@@ -539,10 +570,10 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void k_gather_down_b16(
     return;
   }
   for (int it = wave; it < nsl * tpw; it += GATHER_WAVES) {
-    const int slice = xcd + 8 * (it / tpw);
+    const int slice = slice_of(it / tpw);
     const int i = it % tpw;
     const int64_t col = (int64_t)slice * SLICE2 + sub * 8;
-    const uint32_t col_b = (uint32_t)(slice * f * SLICE2 * 2) + (uint32_t)sub * 16u;
+    const uint32_t col_b = slice_byte(slice) + (uint32_t)sub * 16u;
     {
       const int nnz = __builtin_amdgcn_readfirstlane(cnt_s[i]);
       if (nnz < 0) continue;
@@ -550,7 +581,7 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void k_gather_down_b16(
       if constexpr (VK == 1)
         slice_token_f32<U>(ent + 2 * i * K, nnz, wr, col_b, grp, acc);
       else
-        slice_token<U>(ent + i * K, nnz, wr, col_b, grp, acc);
+        slice_token<U, RM>(ent + i * K, nnz, wr, col_b, row_b, grp, acc);
       if (grp == 0) store_slice<OUT>(Y, Yf, tok(i) * d + col, acc);
     }
   }
@@ -1029,19 +1060,26 @@ __global__ __launch_bounds__(256) void k_pack_down(const bf16_t* __restrict__ W,
 
 static int slice_walk_tpw(int64_t T, int64_t per_tok);
 
-hipError_t launch_gather_down(int val_bf16, int64_t T, int64_t d, int K, const void* ell_val,
-                              const uint16_t* ell_idx, const int32_t* row_nnz, const uint8_t* row_ovf,
-                              const void* W, void* Y, hipStream_t s) {
+// 32 tokens per workgroup (8 per wave, whose W rows then share the L2) while that leaves at
+// least 1024 workgroups, fewer for smaller batches, down to one token per wave: the walk of a
+// token is a chain of loads, and 32 tokens at T = 64, d = 256 (4 workgroups) took 14.4 us,
+// 4 tokens (32 workgroups) 3.5 us.
+hipError_t launch_gather_down(int64_t T, int64_t d, int K, const float* ell_val, const uint16_t* ell_idx,
+                              const int32_t* row_nnz, const uint8_t* row_ovf, const float* W, float* Y, hipStream_t s,
+                              OvfList ol) {
   if (T == 0) return hipSuccess;
+  if (ol.rows && (T > 64 || !ol.n)) return hipErrorInvalidValue;
   const int n_slices = (int)cdiv(d, SLICE);
-  const int n_tb = (int)cdiv(T, TOK_PER_WG);
+  int tpw = 32;
+  while (tpw > 4 && cdiv(T, tpw) * n_slices < 1024) tpw /= 2;
+  const int n_tb = (int)cdiv(T, tpw);
   const dim3 grid((unsigned)(n_slices * n_tb));
-  if (val_bf16)
-    hipLaunchKernelGGL(k_gather_down<bf16_t>, grid, dim3(256), 0, s, T, d, K, (const bf16_t*)ell_val, ell_idx,
-                       row_nnz, row_ovf, (const bf16_t*)W, (bf16_t*)Y, n_slices, n_tb);
+  if (d % 2 == 0)
+    hipLaunchKernelGGL(k_gather_down<false>, grid, dim3(256), 0, s, T, d, K, ell_val, ell_idx, row_nnz, row_ovf, W, Y,
+                       n_slices, n_tb, tpw, ol);
   else
-    hipLaunchKernelGGL(k_gather_down<float>, grid, dim3(256), 0, s, T, d, K, (const float*)ell_val, ell_idx,
-                       row_nnz, row_ovf, (const float*)W, (float*)Y, n_slices, n_tb);
+    hipLaunchKernelGGL(k_gather_down<true>, grid, dim3(256), 0, s, T, d, K, ell_val, ell_idx, row_nnz, row_ovf, W, Y,
+                       n_slices, n_tb, tpw, ol);
   return hipGetLastError();
 }
 
@@ -1049,11 +1087,12 @@ hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int K, con
                                      const uint16_t* ell_idx, const int32_t* row_nnz, const uint8_t* row_ovf,
                                      const void* Wp, void* Y, hipStream_t s, int val_f32, int out_mode, float* Yf,
                                      const int32_t* order, const int32_t* skip, const float* part_u,
-                                     sfl_stats_t* stats, OvfList ol) {
+                                     sfl_stats_t* stats, OvfList ol, bool row_major) {
   if (T == 0) return hipSuccess;
   if (ol.rows && (T > 64 || !ol.n)) return hipErrorInvalidValue;
   if (part_u && (val_f32 || out_mode != 0)) return hipErrorInvalidValue;
-  if (d % (8 * SLICE2) != 0) return hipErrorInvalidValue;
+  if (row_major && (val_f32 || out_mode != 0 || part_u || f * d * 2 >= (int64_t)1 << 31)) return hipErrorInvalidValue;
+  if (d % (row_major ? SLICE2 : 8 * SLICE2) != 0) return hipErrorInvalidValue;
   if (out_mode < 0 || out_mode > 2 || (out_mode > 0 && !Yf) || (out_mode != 1 && !Y)) return hipErrorInvalidValue;
   const int n_slices = (int)(d / SLICE2);
   const int vk = val_f32 ? 1 : 0;
@@ -1081,17 +1120,18 @@ hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int K, con
   if (lds > 160 * 1024) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(8 * blocks)), block(GATHER_WAVES * 64);
   const bool short_rows = use_short_unroll(K, (int64_t)lds);
-#define SFL_GATHER_LAUNCH_G(VK_, OUT_, U_, TG_)                                                                     \
+#define SFL_GATHER_LAUNCH_R(VK_, OUT_, U_, TG_, RM_)                                                                \
   do {                                                                                                             \
     if (lds > 65536) {                                                                                             \
-      const hipError_t e = hipFuncSetAttribute((const void*)k_gather_down_b16<VK_, OUT_, U_, TG_>,                 \
+      const hipError_t e = hipFuncSetAttribute((const void*)k_gather_down_b16<VK_, OUT_, U_, TG_, RM_>,            \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);              \
       if (e != hipSuccess) return e;                                                                               \
     }                                                                                                              \
-    hipLaunchKernelGGL((k_gather_down_b16<VK_, OUT_, U_, TG_>), grid, block, lds, s, T, d, f, K, ell_val, ell_idx, \
-                       row_nnz, row_ovf, (const bf16_t*)Wp, (bf16_t*)Y, Yf, n_slices, tpw, order, skip, part_u,    \
-                       stats, ol);                                                                                 \
+    hipLaunchKernelGGL((k_gather_down_b16<VK_, OUT_, U_, TG_, RM_>), grid, block, lds, s, T, d, f, K, ell_val,     \
+                       ell_idx, row_nnz, row_ovf, (const bf16_t*)Wp, (bf16_t*)Y, Yf, n_slices, tpw, order, skip,   \
+                       part_u, stats, ol);                                                                         \
   } while (0)
+#define SFL_GATHER_LAUNCH_G(VK_, OUT_, U_, TG_) SFL_GATHER_LAUNCH_R(VK_, OUT_, U_, TG_, false)
 #define SFL_GATHER_LAUNCH_U(VK_, OUT_, U_) SFL_GATHER_LAUNCH_G(VK_, OUT_, U_, false)
 #define SFL_GATHER_LAUNCH(VK_, OUT_)                  \
   do {                                                \
@@ -1100,7 +1140,9 @@ hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int K, con
     else                                              \
       SFL_GATHER_LAUNCH_U(VK_, OUT_, GU);             \
   } while (0)
-  if (groups && vk == 0 && out_mode == 0) SFL_GATHER_LAUNCH_G(0, 0, GU_GROUP, true);
+  if (row_major && groups) SFL_GATHER_LAUNCH_R(0, 0, GU_GROUP, true, true);
+  else if (row_major) SFL_GATHER_LAUNCH_R(0, 0, GU_BF16, false, true);
+  else if (groups && vk == 0 && out_mode == 0) SFL_GATHER_LAUNCH_G(0, 0, GU_GROUP, true);
   else if (groups && vk == 1 && out_mode == 0) SFL_GATHER_LAUNCH_G(1, 0, GU_GROUP, true);
   else if (groups && vk == 1 && out_mode == 1) SFL_GATHER_LAUNCH_G(1, 1, GU_GROUP, true);
   else if (groups && vk == 1 && out_mode == 2) SFL_GATHER_LAUNCH_G(1, 2, GU_GROUP, true);
@@ -1112,6 +1154,7 @@ hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int K, con
 #undef SFL_GATHER_LAUNCH
 #undef SFL_GATHER_LAUNCH_U
 #undef SFL_GATHER_LAUNCH_G
+#undef SFL_GATHER_LAUNCH_R
   return hipGetLastError();
 }
 

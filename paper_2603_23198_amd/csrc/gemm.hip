@@ -1,4 +1,4 @@
-// Dense GEMMs of the FFN layer: bf16 on MFMA and fp32 on FMA.
+// Dense GEMMs of the FFN layer: bf16 and fp32, on MFMA.
 //
 // Two bf16 kernels, both 256x256 output tiles per workgroup of 8 waves:
 //  * k_gemm_kc (both operands K-contiguous, K % 64 == 0; the forward's X W_up^T, the
@@ -1293,14 +1293,16 @@ int device_cus() {
 // work per byte loaded and wins wherever its tiles fill the CUs; up to about a thousand rows
 // they do not: T = 509, d = 2048, f = 5632 (44, 88 or 176 tiles) 57, 35 and 26 us, T = 300,
 // d = 4096, f = 16384 (128, 192 or 320) 99, 61 and 90 us, T = 1024 (256, 512 or 1024) 115, 141
-// and 200 us.
+// and 200 us. Smaller tiles have to promise a gain of 15 %: a last round that is mostly empty
+// costs the 256-row tiles less than a full one (T = 1500, f = 16384: 2 rounds against 3 of
+// 128-row tiles, 218 and 214 us).
 int kc_tile_rows(const GemmParams& p) {
   constexpr int rows[] = {256, 128, 64}, cost[] = {100, 62, 47};
   int best = BM;
-  int64_t least = INT64_MAX;
+  int64_t least = 0;
   for (int i = 0; i < 3; ++i) {
     const int64_t c = cdiv(cdiv(p.M, rows[i]) * cdiv(p.N, BN), device_cus()) * cost[i];
-    if (c < least) {
+    if (i == 0 || c * 115 < least * 100) {
       least = c;
       best = rows[i];
     }
@@ -1401,70 +1403,151 @@ hipError_t launch_twell(const GemmParams& p, hipStream_t s) {
   }
 }
 
-// ---- fp32 FMA GEMM (A [M][K] row-major, B [K][N] row-major), 64x64 tiles ------------------
-template <int EPI>
+// ---- fp32 GEMM (A [M][K] row-major, B [K][N] row-major), v_mfma_f32_16x16x4_f32 -----------
+// BT x BT output tiles, four waves of BT/2 x BT/2 each, K in steps of BKF: the next step's
+// operands are fetched into registers while the current one, in LDS, feeds the MFMAs. The
+// layer's fp32 batches are small and latency bound, so a step is as deep as the registers
+// allow (at BT = 32, d = 256 takes two), and 32 x 32 tiles are used where 64 x 64 ones leave
+// CUs idle: at T = 64, d = 256, f = 1024 the up GEMM takes
+// 6.3 us with 64 tiles of 32 x 32 (16-k steps on 16 tiles of 64 x 64, without MFMA: 35.7); the
+// forward at T = 512, d = 1024, f = 4096 went 246 -> 78 us.
+// LDS rows are padded by 4 floats: A's [m][k] rows are then read 16 bytes (four k) per lane
+// and B's [k][n] rows 4 bytes per lane without bank conflicts. The MFMA j of a 16-k group
+// takes k = 4 (lane / 16) + j of both operands.
+template <int BT> struct F32Geo {
+  static constexpr int BKF = BT == 64 ? 64 : 128;      // k per step
+  static constexpr int LDA = BKF + 4, LDB = BT + 4;    // padded LDS row lengths
+  static constexpr int CA = BT * BKF / 4 / 256;        // 16-byte chunks per thread (same for B)
+  static constexpr int NB = BT / 32;                   // 16 x 16 blocks per wave and dimension
+};
+
+// VEC: K and N multiples of 4 and 16-byte aligned operands (else element-wise loads).
+template <int EPI, int BT, bool VEC>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmParams p) {
-  __shared__ float As[16][64 + 1];
-  __shared__ float Bs[16][64 + 1];
-  const int tid = threadIdx.x;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  typedef F32Geo<BT> G;
+  __shared__ __attribute__((aligned(16))) float As[BT * G::LDA];
+  __shared__ __attribute__((aligned(16))) float Bs[G::BKF * G::LDB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0 && blockIdx.y == 0) zero_first(p);
+  const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
   const int m_eff = p.m_count ? min(*p.m_count, p.count_cap) : p.M;
   if (m0 >= m_eff) return;
   const float* A = (const float*)p.A;
   const float* B = (const float*)p.B;
-  const int tr = tid / 16, tc = tid % 16;  // 16x16 threads, 4x4 outputs each
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < p.K; k0 += 16) {
-    for (int e = tid; e < 64 * 16; e += 256) {
-      const int r = e / 16, k = e % 16;
-      const int gm = m0 + r, gk = k0 + k;
-      float v = 0.f;
-      if (gm < m_eff && gk < p.K) {
-        const int64_t sr = p.a_rows ? p.a_rows[gm] : gm;
-        v = A[sr * p.lda + gk];
+  // thread's chunks c = tid + 256 u: A row c / (BKF / 4), k 4 (c % (BKF / 4)); B row (k)
+  // c / (BT / 4), columns 4 (c % (BT / 4))
+  const float* arow[G::CA];
+#pragma unroll
+  for (int u = 0; u < G::CA; ++u) {
+    const int gm = m0 + (tid + 256 * u) / (G::BKF / 4);
+    arow[u] = gm < m_eff ? A + (p.a_rows ? (int64_t)p.a_rows[gm] : (int64_t)gm) * p.lda : nullptr;
+  }
+  f32x4_t ra[G::CA], rb[G::CA];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < G::CA; ++u) {
+      const int c = tid + 256 * u;
+      const int ka = k0 + (c % (G::BKF / 4)) * 4;
+      const int kb = k0 + c / (BT / 4), nb = n0 + (c % (BT / 4)) * 4;
+      const float* br = B + (int64_t)kb * p.ldb + nb;
+      f32x4_t va = {0.f, 0.f, 0.f, 0.f}, vb = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (VEC) {
+        if (arow[u] && ka < p.K) va = *(const f32x4_t*)(arow[u] + ka);
+        if (kb < p.K && nb < p.N) vb = *(const f32x4_t*)br;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (arow[u] && ka + e < p.K) va[e] = arow[u][ka + e];
+          if (kb < p.K && nb + e < p.N) vb[e] = br[e];
+        }
       }
-      As[k][r] = v;
-      const int kk = e / 64, n = e % 64;
-      const int gk2 = k0 + kk, gn = n0 + n;
-      Bs[kk][n] = (gk2 < p.K && gn < p.N) ? B[(int64_t)gk2 * p.ldb + gn] : 0.f;
+      ra[u] = va;
+      rb[u] = vb;
+    }
+  };
+  f32x4_t acc[G::NB][G::NB];
+#pragma unroll
+  for (int i = 0; i < G::NB; ++i)
+#pragma unroll
+    for (int j = 0; j < G::NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int wm = (wave & 1) * (BT / 2), wn = (wave >> 1) * (BT / 2);
+  fetch(0);
+  for (int k0 = 0; k0 < p.K; k0 += G::BKF) {
+#pragma unroll
+    for (int u = 0; u < G::CA; ++u) {
+      const int c = tid + 256 * u;
+      *(f32x4_t*)(As + c / (G::BKF / 4) * G::LDA + (c % (G::BKF / 4)) * 4) = ra[u];
+      *(f32x4_t*)(Bs + c / (BT / 4) * G::LDB + (c % (BT / 4)) * 4) = rb[u];
     }
     __syncthreads();
+    if (k0 + G::BKF < p.K) fetch(k0 + G::BKF);
+#pragma unroll 4
+    for (int kk = 0; kk < G::BKF; kk += 16) {  // k past the end holds zeros
+      const int kq = kk + 4 * (lane >> 4);
+      f32x4_t a[G::NB];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
+      for (int i = 0; i < G::NB; ++i) a[i] = *(const f32x4_t*)(As + (wm + i * 16 + (lane & 15)) * G::LDA + kq);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][tr * 4 + i];
+      for (int e = 0; e < 4; ++e) {
+        float b[G::NB];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tc * 4 + j];
+        for (int j = 0; j < G::NB; ++j) b[j] = Bs[(kq + e) * G::LDB + wn + j * 16 + (lane & 15)];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < G::NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+          for (int j = 0; j < G::NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j], acc[i][j], 0, 0, 0);
+      }
     }
     __syncthreads();
   }
+  float l1 = 0.f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + tr * 4 + i;
-    if (row >= m_eff) continue;
-    const int64_t crow = p.c_rows ? (int64_t)p.c_rows[row] : (int64_t)row;
-    float sh = 0.f;
-    if (p.shift) sh = p.shift[p.s_rows ? p.s_rows[row] : row];
+  for (int i = 0; i < G::NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tc * 4 + j;
-      if (col >= p.N) continue;
-      float v = acc[i][j];
-      if (EPI == EPI_F32 || EPI == EPI_ACT_RELU) {
-        if (p.bias) v += p.bias[col];
-        v += sh;
+    for (int r = 0; r < 4; ++r) {
+      const int row = m0 + wm + i * 16 + AccGeo<16>::row(r, lane);
+      if (row >= m_eff) continue;
+      const int64_t crow = p.c_rows ? (int64_t)p.c_rows[row] : (int64_t)row;
+      float sh = 0.f;
+      if (p.shift) sh = p.shift[p.s_rows ? p.s_rows[row] : row];
+#pragma unroll
+      for (int j = 0; j < G::NB; ++j) {
+        const int col = n0 + wn + j * 16 + AccGeo<16>::col(lane);
+        if (col >= p.N) continue;
+        float v = acc[i][j][r];
+        if (EPI == EPI_F32 || EPI == EPI_ACT_RELU) {
+          if (p.bias) v += p.bias[col];
+          v += sh;
+        }
+        if (EPI == EPI_ACT_RELU) {
+          v = active_bits(v) ? v : 0.f;
+          l1 += v;
+        }
+        ((float*)p.C)[crow * p.ldc + col] = v;
       }
-      float* C = (float*)p.C;
-      if (EPI == EPI_F32) C[crow * p.ldc + col] = v;
-      else if (EPI == EPI_ACT_RELU) C[crow * p.ldc + col] = active_bits(v) ? v : 0.f;
-      else if (EPI == EPI_ACT) C[crow * p.ldc + col] = v;
+    }
+  if (EPI == EPI_ACT_RELU && p.l1_stats) {
+    // the sum of the stored values, one float64 atomic per block
+    __shared__ float wl1[4];
+    l1 = wave_sum<float>(l1);
+    if (lane == 0) wl1[wave] = l1;
+    __syncthreads();
+    if (tid == 0) {
+      const float tot = (wl1[0] + wl1[1]) + (wl1[2] + wl1[3]);
+      if (tot != 0.f) atomicAdd(&p.l1_stats->l1_sum, (double)tot);
     }
   }
+}
+
+template <int EPI, int BT>
+hipError_t launch_f32(const GemmParams& p, hipStream_t s) {
+  const dim3 grid((unsigned)cdiv(p.N, BT), (unsigned)cdiv(p.M, BT));
+  const bool vec = p.K % 4 == 0 && p.N % 4 == 0 && p.lda % 4 == 0 && p.ldb % 4 == 0 &&
+                   ((((uintptr_t)p.A) | ((uintptr_t)p.B)) & 15) == 0;
+  if (vec) hipLaunchKernelGGL((k_gemm_f32<EPI, BT, true>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((k_gemm_f32<EPI, BT, false>), grid, dim3(256), 0, s, p);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -1570,14 +1653,14 @@ int gemm_split_count(int alay, int blay, const GemmParams& p) {
 
 hipError_t gemm_f32(int epi, const GemmParams& p, hipStream_t s) {
   if (p.M == 0 || p.N == 0) return hipSuccess;
-  const dim3 grid((unsigned)cdiv(p.N, 64), (unsigned)cdiv(p.M, 64));
+  // 64 x 64 tiles once they give every CU two blocks, else 32 x 32 (more blocks in flight)
+  const bool big = cdiv(p.M, 64) * cdiv(p.N, 64) >= 2 * device_cus();
   switch (epi) {
-    case EPI_F32: hipLaunchKernelGGL(k_gemm_f32<EPI_F32>, grid, dim3(256), 0, s, p); break;
-    case EPI_ACT_RELU: hipLaunchKernelGGL(k_gemm_f32<EPI_ACT_RELU>, grid, dim3(256), 0, s, p); break;
-    case EPI_ACT: hipLaunchKernelGGL(k_gemm_f32<EPI_ACT>, grid, dim3(256), 0, s, p); break;
+    case EPI_F32: return big ? launch_f32<EPI_F32, 64>(p, s) : launch_f32<EPI_F32, 32>(p, s);
+    case EPI_ACT_RELU: return big ? launch_f32<EPI_ACT_RELU, 64>(p, s) : launch_f32<EPI_ACT_RELU, 32>(p, s);
+    case EPI_ACT: return big ? launch_f32<EPI_ACT, 64>(p, s) : launch_f32<EPI_ACT, 32>(p, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace sfl

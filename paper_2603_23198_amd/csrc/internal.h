@@ -10,7 +10,7 @@
 namespace sfl {
 
 // ---------------------------------------------------------------- GEMM ----
-// C = A * B with bf16 operands on MFMA (fp32 accumulate), or fp32 operands on FMA.
+// C = A * B on MFMA with bf16 operands (fp32 accumulate) or fp32 operands.
 // Layouts: A is MK ([M][K], row stride lda) or KM ([K][M]); B is NK ([N][K]) or KN ([K][N]).
 // K-contiguous rows / row-contiguous (K-major) / row-contiguous with the K rows gathered
 enum Layout { LAY_KC = 0, LAY_RC = 1, LAY_RCG_ = 2 };
@@ -81,7 +81,7 @@ struct GemmParams {
   // EPI_GATED_PAIR: the second B operand (W_up^T beside B = W_gate^T, same shape)
   const void* B2;
   // split-K GEMMs of EPI_ACT_RELU (the few-rows kernel's last blocks, else the reduction
-  // launch) and EPI_GATED_PAIR: the sum of the stored |values| is added to
+  // launch), fp32 GEMMs of EPI_ACT_RELU (one atomic per block) and EPI_GATED_PAIR: the sum of the stored |values| is added to
   // l1_stats->l1_sum (one float64 atomic per tile or per reduction block); the reduction
   // launch adds the n_l1_more sums at l1_more as well (another kernel's share)
   sfl_stats_t* l1_stats;
@@ -119,7 +119,8 @@ bool split_gemm_l1(const GemmParams& p, int blay);
 // zero_stats and zero[0 .. n_zero) before anything else.
 bool few_rows_path(const GemmParams& p, int blay);
 
-// fp32 FMA GEMM for the F32 dtype (A MK, B KN only; any sizes).
+// fp32 GEMM for the F32 dtype (A MK, B KN only; any sizes). Clears zero_stats and zero[0 ..
+// n_zero) first; EPI_ACT_RELU with l1_stats adds the sum of the stored values to it.
 hipError_t gemm_f32(int epi, const GemmParams& p, hipStream_t s);
 
 // ----------------------------------------------------------- TwELL ----
@@ -191,10 +192,6 @@ hipError_t launch_ovf_l1(int64_t f, int val_bf16, const void* ovf_dense, const i
                          int n_extra = 0);
 
 // ---------------------------------------------------------- gathers ----
-// Y[t, :] = sum_e ell_val[t][e] * W[ell_idx[t][e], :] for rows with row_ovf[t] == 0.
-hipError_t launch_gather_down(int val_bf16, int64_t T, int64_t d, int ell_width, const void* ell_val,
-                              const uint16_t* ell_idx, const int32_t* row_nnz,
-                              const uint8_t* row_ovf, const void* W, void* Y, hipStream_t s);
 // The dense-backup row list (ascending rows, at most cap of them, the count in *n and, with
 // stats, its row count and capacity flag), built by another kernel in passing.
 struct OvfList {
@@ -203,6 +200,11 @@ struct OvfList {
   int32_t cap = 0;
   sfl_stats_t* stats = nullptr;
 };
+// fp32: Y[t, :] = sum_e ell_val[t][e] * W[ell_idx[t][e], :] for rows with row_ovf[t] == 0. With
+// ol.rows (at most 64 rows): block 0 also builds the dense-backup row list from row_ovf.
+hipError_t launch_gather_down(int64_t T, int64_t d, int ell_width, const float* ell_val, const uint16_t* ell_idx,
+                              const int32_t* row_nnz, const uint8_t* row_ovf, const float* W, float* Y, hipStream_t s,
+                              OvfList ol = OvfList());
 // order[0 .. T): the sparse rows by descending row_nnz, then the dense-backup rows (one
 // workgroup, counting sort over K + 2 buckets; order within a bucket unspecified; with
 // row_ovf null every row counts as sparse and counts above K share the first bucket).
@@ -214,7 +216,8 @@ bool nnz_order_supported(int K);
 hipError_t launch_nnz_order(int64_t T, int K, const int32_t* row_nnz, const uint8_t* row_ovf, int32_t* order,
                             hipStream_t s, const OvfList* list = nullptr, const ClassifyPart* parts = nullptr,
                             int n_parts = 0);
-// bf16, d % 512 == 0: same sum from the slice-major copy of W_down (persistent, XCD-aware).
+// bf16, d % 512 == 0: same sum from the slice-major copy of W_down (XCD-aware); row_major
+// (d % 64 == 0; bf16 values, out_mode 0): from W_down [f][d] itself.
 // out_mode 0: bf16 Y; 1: fp32 Yf; 2: bf16 Y of (sum + Yf) (val_f32 only for 1 and 2).
 // With ol.rows (at most 64 rows): block 0 also builds the dense-backup row list from row_ovf
 // (as launch_ovf_list would), before anything else.
@@ -227,7 +230,7 @@ hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int ell_wi
                                      int val_f32 = 0, int out_mode = 0, float* Yf = nullptr,
                                      const int32_t* order = nullptr, const int32_t* skip = nullptr,
                                      const float* part_u = nullptr, sfl_stats_t* stats = nullptr,
-                                     OvfList ol = OvfList());
+                                     OvfList ol = OvfList(), bool row_major = false);
 // Gated backward at the ELL entries: dh (8 partials + lambda' sign(g u)) -> dh_u, dh_g, h.
 hipError_t launch_gated_entry_grads(int64_t T, int K, const void* ell_val, const int32_t* row_nnz,
                                     const uint8_t* row_ovf, const float* part, const float* u, float lam, float* dhu,

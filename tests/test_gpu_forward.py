@@ -432,6 +432,54 @@ def test_ragged_shapes_bf16(T, d, f, Tn, S, K):
     check_pattern(twell_views(bufs, T, f, cfg), Z, np.arange(min(T, 64)), f, Tn, S)
 
 
+@pytest.mark.parametrize("T,d,f", [(1, 1, 1), (33, 7, 65), (64, 130, 1000), (31, 129, 1023), (65, 515, 257),
+                                   (257, 66, 642), (520, 128, 4096), (513, 67, 4097), (40, 1024, 4096)])
+@pytest.mark.parametrize("every", [0, 5])
+def test_fp32_sizes(T, d, f, every):
+    """fp32 at odd and ragged sizes (32 x 32 and 64 x 64 GEMM tiles, 16-byte and element-wise
+    loads, K tails, odd d in the gather), with and without dense-backup rows: Y, the row list
+    and the L1 sum against the fp64 oracle, and nothing written past Y."""
+    w = wl.make_ffn("fp32 sizes", "f32", T, d, f, seed=T + f, sparsity=0.95, ell_width=max(4, f // 8))
+    if every:
+        w.shift_t[::every] = 50.0  # every unit active: dense-backup rows
+    X, Wu, Wd = dev(w.X), dev(w.W_up), dev(w.W_down)
+    cfg = b.make_cfg(**w.cfg)
+    bufs, stats = b.alloc_twell(T, f, "f32", cfg), b.alloc_stats()
+    out = torch.full((T * d + 64,), 7.0, dtype=torch.float32, device="cuda")
+    kw = dict(Y=out[:T * d].view(T, d), bufs=bufs, shift_t=dev(w.shift_t), stats=stats)
+    ws = torch.empty(max(1, b.sfl_workspace_size(b.ffn_args(X, Wu, Wd, cfg, **kw))), dtype=torch.uint8, device="cuda")
+    b.sfl_ffn_forward(b.ffn_args(X, Wu, Wd, cfg, workspace=ws, **kw))
+    torch.cuda.synchronize()
+    Yref, Z, H = ffn.ffn_dense(w.as_f64(w.X), w.as_f64(w.W_up), w.as_f64(w.W_down), None, w.shift_t)
+    # 1e-5 of the largest row: a single active unit's pre-activation can be a small difference
+    # of large sums, so rows are not compared one by one
+    assert np.linalg.norm(to_f64(kw["Y"]) - Yref) <= 1e-5 * max(np.linalg.norm(Yref), 1.0)
+    assert bool((out[T * d:] == 7.0).all())
+    got = twell_views(bufs, T, f, cfg)
+    assert list(got["ovf_rows"][:got["n_ovf"]]) == list(np.nonzero(got["row_ovf"])[0])
+    st = b.read_stats(stats)
+    assert st["n_ovf_rows"] == got["n_ovf"] and st["total_nnz"] == got["row_nnz"].sum()
+    assert abs(st["l1_sum"] - H.sum()) <= 1e-5 * max(H.sum(), 1.0)
+
+
+@pytest.mark.parametrize("T,d,f,K", [(1, 64, 256, 32), (7, 192, 1024, 64), (64, 704, 512, 48), (200, 960, 1024, 320),
+                                     (1030, 192, 1024, 64), (1100, 1600, 2048, 300), (2100, 448, 1088, 96)])
+def test_widths_not_a_multiple_of_512(T, d, f, K):
+    """bf16 widths whose 64-column slices do not deal out evenly over the XCDs (1 to 25 slices:
+    none, one or three of each XCD's own, one to seven left over), both walks, with dense-backup
+    and empty rows: every row of Y against the oracle."""
+    w = wl.make_ffn("other widths", "bf16", T, d, f, seed=d, sparsity=0.97, ell_width=K, tile_slots=64)
+    w.shift_t[::11] = 50.0
+    w.shift_t[3::11] = -1e4
+    Y, bufs, _, cfg = run_forward(w, use_wupt=T % 2 == 0)
+    Yref, _ = oracle_rows(w, np.arange(T))
+    Yg = to_f64(Y)
+    assert rel_l2(Yg, Yref) <= 2e-2
+    sparse = np.nonzero(host_bits(bufs["row_ovf"])[:T] == 0)[0]
+    for t in sparse:
+        assert np.linalg.norm(Yg[t] - Yref[t]) <= 2e-2 * np.linalg.norm(Yref[t]), t
+
+
 def test_all_active_and_all_inactive_rows():
     w = wl.make_ffn("extremes", "bf16", 96, 256, 512, seed=3, sparsity=0.95, ell_width=32)
     w.shift_t[:8] = 100.0     # every unit active -> dense-backup rows
