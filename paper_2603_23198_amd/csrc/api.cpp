@@ -415,6 +415,9 @@ sfl_status_t sfl_pack_twell(const float* Z, int64_t T, int64_t f, sfl_dtype_t va
     SFL_HIP(launch_pack_classify_rows(Z, 0, nullptr, nullptr, T, f, vb, cfg->tile_cols, cfg->tile_slots,
                                       cfg->ell_width, out->val, out->idx, out->cnt, out->row_nnz, out->row_ovf,
                                       out->ell_val, out->ell_idx, stats, s, 1, pk));
+  } else if (pack_rows_ok(T, f, cfg->tile_cols, cfg->ell_width, vb) && ((uintptr_t)Z & 15) == 0) {
+    SFL_HIP(launch_pack_rows(Z, T, f, vb, cfg->tile_cols, cfg->tile_slots, cfg->ell_width, out->val, out->idx,
+                             out->cnt, out->row_nnz, out->row_ovf, out->ell_val, out->ell_idx, stats, s, 1, pk));
   } else {
     SFL_HIP(launch_pack_twell(Z, T, f, vb, cfg->tile_cols, cfg->tile_slots, out->val, out->idx, out->cnt, s, pk));
     SFL_HIP(launch_classify(T, f, vb, cfg->tile_cols, cfg->tile_slots, cfg->ell_width, out->val, out->idx, out->cnt,
@@ -627,6 +630,11 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
                                             a->cfg.tile_slots, a->cfg.ell_width, tw.val, tw.idx, tw.cnt, tw.row_nnz,
                                             tw.row_ovf, tw.ell_val, tw.ell_idx, a->stats, s, l1_vals,
                                             packed_layout(a->cfg)));
+          classified = true;
+        } else if (pack_rows_ok(T, f, a->cfg.tile_cols, a->cfg.ell_width, vb) && ((uintptr_t)plan.Z & 15) == 0) {
+          SFL_HIP(launch_pack_rows(plan.Z, T, f, vb, a->cfg.tile_cols, a->cfg.tile_slots, a->cfg.ell_width, tw.val,
+                                   tw.idx, tw.cnt, tw.row_nnz, tw.row_ovf, tw.ell_val, tw.ell_idx, a->stats, s,
+                                   l1_vals, packed_layout(a->cfg)));
           classified = true;
         } else {
           SFL_HIP(launch_pack_twell(plan.Z, T, f, vb, a->cfg.tile_cols, a->cfg.tile_slots, tw.val, tw.idx, tw.cnt,

@@ -606,6 +606,195 @@ hipError_t launch_pack_classify_rows(const float* Z, int ks, const float* bias, 
   return hipGetLastError();
 }
 
+// Larger batches: the TwELL pack (Alg. 1) and the hybrid classification (Sec. 3.4) of a row
+// by four waves, a quarter of its columns each, so that Z is read once at 16 bytes per lane
+// with kPackRowsUnroll loads in flight, and the slabs are not read back. A step is 256
+// consecutive columns, four per lane (as in k_pack_classify_rows): a TwELL tile is T_n / 4
+// lanes, the ballots below a lane in its tile give the slot, those below it in the wave, after
+// the quarter's entries so far, its place among the quarter's ELL entries. These wait in LDS
+// for the row's total (a dense-backup row's are not written) and the counts of the quarters
+// before. Bound by the latency of reading Z: T = 4001, f = 5600 (90 MB) takes about 33 us (one
+// wave per row: 39; one wave per (row, tile) at 4 bytes per lane 32, then the classification 12).
+constexpr int kPackRowsWaves = 16;                   // per block
+constexpr int kPackRowsParts = 4;                    // waves per row
+constexpr int kPackRowsUnroll = 6;
+constexpr int kPackRowsPerBlock = kPackRowsWaves / kPackRowsParts;
+constexpr size_t kPackRowsLds = 64 * 1024;
+constexpr uint32_t kPackNoStore = 0x80000000u;       // an offset past every slab
+
+template <typename V, bool PK, int TN>
+__global__ __launch_bounds__(kPackRowsWaves * 64) void k_pack_rows(
+    const float* __restrict__ Z, int64_t T, int f, int S, int NT, int K, V* __restrict__ val,
+    uint16_t* __restrict__ idx, int32_t* __restrict__ cnt, int32_t* __restrict__ row_nnz, uint8_t* __restrict__ row_ovf,
+    V* __restrict__ ell_val, uint16_t* __restrict__ ell_idx, sfl_stats_t* __restrict__ stats, int l1_vals) {
+  extern __shared__ __align__(16) unsigned char pr_lds[];
+  __shared__ int w_cnt[2][kPackRowsWaves], w_over[2][kPackRowsWaves];  // by turns, one pass after the other
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int part = w % kPackRowsParts;
+  // [waves][K + 1] values, [waves][K + 1] columns; entries that are not kept go to place K
+  V* const ev = (V*)pr_lds + (size_t)w * (K + 1);
+  uint16_t* const ec = (uint16_t*)((V*)pr_lds + (size_t)kPackRowsWaves * (K + 1)) + (size_t)w * (K + 1);
+  constexpr int GL = TN / 4;  // lanes per TwELL tile
+  const int gsh = l & ~(GL - 1);
+  const uint64_t gbits = GL == 64 ? ~0ull : (1ull << GL) - 1ull;
+  const int64_t row_words = (int64_t)NT * (PK ? 32 : S);
+  const bool keep = ell_val || l1_vals;
+  const int per = (int)cdiv(cdiv(f, 256), kPackRowsParts) * 256;
+  const int c_lo = min(f, part * per), c_hi = min(f, c_lo + per);
+  int64_t nnz_sum = 0;
+  int over_sum = 0;
+  float l1 = 0.f;
+  int turn = 0;
+  for (int64_t t0 = (int64_t)blockIdx.x * kPackRowsPerBlock; t0 < T; t0 += (int64_t)gridDim.x * kPackRowsPerBlock) {
+    const int64_t t = t0 + w / kPackRowsParts;
+    int mine = 0, over = 0;
+    if (t < T) {
+      const float* zr = Z + t * f;
+      // the row's slabs: stores at an offset past a slab's end (lanes without an entry, slots
+      // from S on) write nothing
+      constexpr int es = PK ? 4 : (int)sizeof(V);
+      const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)((char*)val + t * row_words * es), (short)0, (int)(row_words * es), 0x00020000);
+      const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc(
+          PK ? (void*)val : (void*)(idx + t * row_words), (short)0, (int)(row_words * 2), 0x00020000);
+      int32_t* const rc = PK ? nullptr : cnt + t * NT;
+      for (int c0 = c_lo; c0 < c_hi; c0 += 256 * kPackRowsUnroll) {
+        float4 z[kPackRowsUnroll];  // columns past the row re-read its last four and are not active
+#pragma unroll
+        for (int u = 0; u < kPackRowsUnroll; ++u) z[u] = *(const float4*)(zr + (uint32_t)min(c0 + u * 256 + 4 * l, f - 4));
+#pragma unroll
+        for (int u = 0; u < kPackRowsUnroll; ++u) {
+          const int col = c0 + u * 256 + 4 * l;
+          if (c0 + u * 256 >= c_hi) break;
+          const bool in = col < f;
+          const float zz[4] = {z[u].x, z[u].y, z[u].z, z[u].w};
+          // entries below the lane in the wave, entries of the wave, and (tiles narrower than
+          // the wave's 256 columns) those of the lane's tile and of the tiles before it
+          uint64_t m[4];
+          int pos = 0, all = 0, cnt_tile = 0, left = 0;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            m[r] = ballot(in && is_active(zz[r]));
+            pos += mbcnt(m[r]);
+            all += __popcll(m[r]);
+            if constexpr (GL < 64) {
+              cnt_tile += __popc((uint32_t)((m[r] >> gsh) & gbits));
+              left += __popcll(m[r] & ((1ull << gsh) - 1ull));
+            }
+          }
+          if constexpr (GL == 64) cnt_tile = all;
+          int slot = pos - left;
+          pos += mine;
+          mine += all;
+          const int j = col / TN;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (m[r] == 0) continue;  // uniform
+            const bool act = in && is_active(zz[r]);
+            const uint16_t c16 = (uint16_t)(col + r);
+            const V v = VT<V>::cvt(zz[r]);
+            const uint32_t at = (uint32_t)(PK ? j * 32 + 1 + slot : j * S + slot);
+            const bool st = act && slot < S;
+            if constexpr (PK) {
+              __builtin_amdgcn_raw_buffer_store_b32((uint32_t)c16 | ((uint32_t)v << 16), rv, st ? at * 4u : kPackNoStore,
+                                                    0, 0);
+            } else {
+              if constexpr (sizeof(V) == 2)
+                __builtin_amdgcn_raw_buffer_store_b16(v, rv, st ? at * 2u : kPackNoStore, 0, 0);
+              else
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rv, st ? at * 4u : kPackNoStore, 0, 0);
+              __builtin_amdgcn_raw_buffer_store_b16(c16, ri, st ? at * 2u : kPackNoStore, 0, 0);
+            }
+            const int place = act ? min(pos, K) : K;
+            ev[place] = v;
+            ec[place] = c16;
+            slot += act ? 1 : 0;
+            pos += act ? 1 : 0;
+          }
+          const bool first = in && l == gsh;
+          if (first) {
+            if constexpr (PK) __builtin_amdgcn_raw_buffer_store_b32((uint32_t)cnt_tile, rv, (uint32_t)j * 128u, 0, 0);
+            else rc[(uint32_t)j] = cnt_tile;
+          }
+          over += __popcll(ballot(first && cnt_tile > S));
+        }
+      }
+    }
+    if (l == 0) {
+      w_cnt[turn][w] = mine;
+      w_over[turn][w] = over;
+    }
+    __syncthreads();
+    int total = 0, before = 0;
+    over = 0;
+#pragma unroll
+    for (int q = 0; q < kPackRowsParts; ++q) {
+      const int c = w_cnt[turn][w - part + q];
+      before += q < part ? c : 0;
+      total += c;
+      over += w_over[turn][w - part + q];
+    }
+    turn ^= 1;
+    if (t >= T) continue;
+    const bool ovf = total > K || over > 0;
+    if (part == 0) {
+      if (l == 0) {
+        row_nnz[t] = total;
+        row_ovf[t] = ovf ? 1 : 0;
+      }
+      nnz_sum += total;
+      over_sum += over;
+    }
+    if (!ovf && keep) {
+      for (int e = l; e < mine; e += 64) {
+        const V v = ev[e];
+        if (l1_vals) l1 += VT<V>::load(&v, 0);
+        if (ell_val) {
+          ell_val[t * (int64_t)K + before + e] = v;
+          ell_idx[t * (int64_t)K + before + e] = ec[e];
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();  // all lanes are done with the quarter's entries
+  }
+  if (stats) block_stats_add(stats, nnz_sum, over_sum, l1);
+}
+
+// Rows of whole 16-byte chunks, tiles of 64, 128 or 256 columns, and ELL entries that fit the
+// waves' LDS; batches of more than kRowPackMaxRows rows (the one-workgroup-per-row kernel
+// spreads smaller ones over more of the GPU).
+bool pack_rows_ok(int64_t T, int64_t f, int Tn, int K, int val_bf16) {
+  if (T <= kRowPackMaxRows || f % 4 != 0 || f < 4 || f > 65535) return false;
+  if (Tn != 64 && Tn != 128 && Tn != 256) return false;
+  return (size_t)kPackRowsWaves * (K + 1) * (2 + (val_bf16 ? 2 : 4)) <= kPackRowsLds;
+}
+
+hipError_t launch_pack_rows(const float* Z, int64_t T, int64_t f, int val_bf16, int Tn, int S, int K, void* val,
+                            uint16_t* idx, int32_t* cnt, int32_t* row_nnz, uint8_t* row_ovf, void* ell_val,
+                            uint16_t* ell_idx, sfl_stats_t* stats, hipStream_t s, int l1_vals, bool packed) {
+  if (!pack_rows_ok(T, f, Tn, K, val_bf16) || ((uintptr_t)Z & 15)) return hipErrorInvalidValue;
+  if (packed && (!val_bf16 || S != 31)) return hipErrorInvalidValue;
+  const int NT = (int)cdiv(f, Tn);
+  const size_t lds = (size_t)kPackRowsWaves * (K + 1) * (2 + (val_bf16 ? 2 : 4));
+  // at most 512 blocks (two per CU): their statistics are added by same-address atomics
+  const dim3 grid((unsigned)std::min<int64_t>(cdiv(T, kPackRowsPerBlock), 512)), block(kPackRowsWaves * 64);
+#define SFL_PACK_ROWS_TN(V_, PK_, TN_)                                                                            \
+  hipLaunchKernelGGL((k_pack_rows<V_, PK_, TN_>), grid, block, lds, s, Z, T, (int)f, S, NT, K, (V_*)val, idx, cnt, \
+                     row_nnz, row_ovf, (V_*)ell_val, ell_idx, stats, l1_vals)
+#define SFL_PACK_ROWS(V_, PK_)                      \
+  do {                                              \
+    if (Tn == 256) SFL_PACK_ROWS_TN(V_, PK_, 256);  \
+    else if (Tn == 128) SFL_PACK_ROWS_TN(V_, PK_, 128); \
+    else SFL_PACK_ROWS_TN(V_, PK_, 64);             \
+  } while (0)
+  if (packed) SFL_PACK_ROWS(bf16_t, true);
+  else if (val_bf16) SFL_PACK_ROWS(bf16_t, false);
+  else SFL_PACK_ROWS(float, false);
+#undef SFL_PACK_ROWS
+#undef SFL_PACK_ROWS_TN
+  return hipGetLastError();
+}
+
 __global__ __launch_bounds__(256) void k_stats_init(sfl_stats_t* stats, int32_t* zero, int n_zero) {
   if (stats && threadIdx.x == 0) {
     stats->total_nnz = 0;
