@@ -710,11 +710,17 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
       // the same down-projection gather as the non-gated layer with h = g * u
       const void* WuP = a->W_up_packed;
       if (!WuP) {
-        if (!WupT) {
-          SFL_HIP(launch_transpose(a->W_up, plan.WupT, d, f, 2, s));
-          WupT = plan.WupT;
+        // straight from W_up, unless the dense-backup rows' GEMMs read W_gate^T (and then
+        // W_up^T beside it)
+        if (!WupT && !a->W_gateT && pack_transposed_ok(a->W_up, d, f)) {
+          SFL_HIP(launch_pack_transposed(a->W_up, plan.WuP, d, f, s));
+        } else {
+          if (!WupT) {
+            SFL_HIP(launch_transpose(a->W_up, plan.WupT, d, f, 2, s));
+            WupT = plan.WupT;
+          }
+          SFL_HIP(launch_pack_down(WupT, plan.WuP, f, d, s));
         }
-        SFL_HIP(launch_pack_down(WupT, plan.WuP, f, d, s));
         WuP = plan.WuP;
       }
       SFL_HIP(launch_gated_updot(T, d, f, a->cfg.ell_width, tw.ell_idx, tw.row_nnz, tw.row_ovf, a->X, WuP,

@@ -444,14 +444,11 @@ sfl_status_t backward_run(const sfl_ffn_bwd_args_t* a, hipStream_t s) {
       *res = given_packed;
       return hipSuccess;
     }
-    const void* WT = given_T;
-    if (!WT) {
-      const hipError_t e = launch_transpose(W, tmpT, d, f, 2, s);
-      if (e != hipSuccess) return e;
-      WT = tmpT;
-    }
     *res = out;
-    return launch_pack_down(WT, out, f, d, s);
+    if (given_T) return launch_pack_down(given_T, out, f, d, s);
+    if (pack_transposed_ok(W, d, f)) return launch_pack_transposed(W, out, d, f, s);
+    const hipError_t e = launch_transpose(W, tmpT, d, f, 2, s);
+    return e != hipSuccess ? e : launch_pack_down(tmpT, out, f, d, s);
   };
   const void* WdP = a->W_down_packed;
   if (!WdP) {

@@ -1056,6 +1056,35 @@ __global__ __launch_bounds__(256) void k_pack_down(const bf16_t* __restrict__ W,
   *(u32x4_t*)(out + ((s * f + n) * SLICE2 + c8 * 8)) = *(const u32x4_t*)(W + n * d + c * 8);
 }
 
+// Slice-major copy of W^T straight from W [d][f]: out[s][n][c] = W[64 s + c][n]. A block moves
+// one 64 x 64 tile through LDS, whose output is 8 KB in one piece: W is read once and written
+// once, where a transpose followed by k_pack_down moved it twice (d = 4096, f = 14336: 103 +
+// 39 us; this 45). Reads are 16 bytes of a W row per lane, writes 16 bytes (8 c) of one n. LDS
+// rows of 66 values keep both sides' 2- and 4-byte accesses at two lanes per bank.
+__global__ __launch_bounds__(256) void k_pack_transposed(const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
+                                                         int64_t f) {
+  __shared__ bf16_t tile[64][66];  // [c][n]
+  const int64_t s = blockIdx.y, n0 = (int64_t)blockIdx.x * 64;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int q = threadIdx.x + 256 * k;
+    const int c = q >> 3, n = (q & 7) * 8;
+    const u32x4_t v = *(const u32x4_t*)(W + (s * 64 + c) * f + n0 + n);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *(uint32_t*)&tile[c][n + 2 * e] = v[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int q = threadIdx.x + 256 * k;
+    const int n = q >> 3, c = (q & 7) * 8;
+    u32x4_t v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (uint32_t)tile[c + 2 * e][n] | ((uint32_t)tile[c + 2 * e + 1][n] << 16);
+    *(u32x4_t*)(out + ((s * f + n0 + n) * 64 + c)) = v;
+  }
+}
+
 }  // namespace
 
 static int slice_walk_tpw(int64_t T, int64_t per_tok);
@@ -1286,6 +1315,19 @@ hipError_t launch_gated_h(int64_t T, int K, const void* ell_val, const int32_t* 
                                                      : launch_gated_h_blocks(T, K));
   hipLaunchKernelGGL(k_gated_h, dim3(grid), dim3(256), 0, s, T, K, (const bf16_t*)ell_val, row_nnz, row_ovf, part_u,
                      (bf16_t*)h, l1_part ? nullptr : stats, l1_part);
+  return hipGetLastError();
+}
+
+bool pack_transposed_ok(const void* W, int64_t d, int64_t f) {
+  static_assert(SLICE2 == 64, "64 x 64 tiles");
+  return d % 64 == 0 && f % 64 == 0 && ((uintptr_t)W & 15) == 0 && d / 64 <= 65535;
+}
+
+hipError_t launch_pack_transposed(const void* W, void* out, int64_t d, int64_t f, hipStream_t s) {
+  if (!pack_transposed_ok(W, d, f) || ((uintptr_t)out & 15)) return hipErrorInvalidValue;
+  if (d == 0 || f == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_pack_transposed, dim3((unsigned)(f / 64), (unsigned)(d / 64)), dim3(256), 0, s,
+                     (const bf16_t*)W, (bf16_t*)out, f);
   return hipGetLastError();
 }
 
