@@ -204,7 +204,7 @@ FwdPlan plan_forward(const sfl_ffn_args_t& a, void* ws) {
   }
   if (a.gated && !a.W_up_packed && !a.W_upT) p.WupT = c.take((size_t)a.f * a.d * elem_size(a.dtype));
   if (packed_gather(a) && !a.W_down_packed) p.WdP = c.take((size_t)a.f * a.d * 2);
-  if (a.dtype == SFL_BF16) p.order = (int32_t*)c.take((size_t)a.T * 4);
+  if (packed_gather(a)) p.order = (int32_t*)c.take((size_t)a.T * 4);
   if (a.gated && !a.W_up_packed) p.WuP = c.take((size_t)a.f * a.d * 2);
   if (a.gated) {
     const int64_t K = std::max<int64_t>(a.cfg.ell_width, 1);
@@ -215,6 +215,9 @@ FwdPlan plan_forward(const sfl_ffn_args_t& a, void* ws) {
   if (a.dtype == SFL_BF16 && (cap > 0 || small_batch(a))) {
     p.part_rows = (int)std::min<int64_t>(align_rows(std::max<int64_t>(cap, a.T)), kPartRows);
     p.part = (float*)c.take((size_t)p.part_rows * std::max(a.f, a.d) * 4);
+    // other widths keep their token order in the partial sums, which nothing uses between the
+    // pack and the dense-backup rows (a batch too large for them is walked in token order)
+    if (!packed_gather(a) && a.T <= p.part_rows * std::max(a.f, a.d)) p.order = (int32_t*)p.part;
   }
   // counters the forward's first kernel zeroes: the recompute list's length, then one per
   // output tile (256 columns, 128 for the gated pair) of the dense-backup GEMMs of at
@@ -231,7 +234,7 @@ FwdPlan plan_forward(const sfl_ffn_args_t& a, void* ws) {
     p.need_slots = (int32_t*)c.take((size_t)cap * 4);
     p.fill_l1 = (float*)c.take((size_t)ovf_fill_grid((int32_t)cap) * 4);
   }
-  if (a.T > 0 && !list_by_gather(a))
+  if (a.T > 0 && !(list_by_gather(a) && packed_gather(a)))
     p.cls_part = (ClassifyPart*)c.take((size_t)classify_grid(a.T, a.f, a.cfg.tile_cols) * sizeof(ClassifyPart));
   p.bytes = c.used;
   return p;
@@ -646,7 +649,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   ev.record(1, s);
   // 2. hybrid classification (Sec. 3.4), unless done with the pack
   // (the statistics of its blocks summed by the list kernel when that runs)
-  ClassifyPart* cls_part = classified || !a->stats ? nullptr : plan.cls_part;
+  ClassifyPart* cls_part = classified || !a->stats || list_by_gather(*a) ? nullptr : plan.cls_part;
   if (!classified)
     SFL_HIP(launch_classify(T, f, vb, a->cfg.tile_cols, a->cfg.tile_slots, a->cfg.ell_width, tw.val, tw.idx,
                             tw.cnt, tw.row_nnz, tw.row_ovf, tw.ell_val, tw.ell_idx, a->stats, s, l1_vals,
@@ -655,7 +658,8 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   // rows the gather's first block builds it, with the token order a second workgroup of
   // the order kernel, else its own kernel
   OvfList late_list;
-  const bool list_by_order = !list_by_gather(*a) && bf && nnz_token_order(*a);
+  const bool token_order = bf && plan.order && nnz_token_order(*a);
+  const bool list_by_order = !list_by_gather(*a) && token_order;
   const int n_cls_part = cls_part ? (int)classify_grid(T, f, a->cfg.tile_cols) : 0;
   if (list_by_gather(*a) || list_by_order) {
     late_list.rows = tw.ovf_rows;
@@ -691,7 +695,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   const void* WupT = a->W_upT;  // gated: W_up^T, given or built in the workspace when needed
   if (bf) {
     const int32_t* order = nullptr;
-    if (nnz_token_order(*a)) {
+    if (token_order) {
       // with a second workgroup building the dense-backup row list
       SFL_HIP(launch_nnz_order(T, a->cfg.ell_width, tw.row_nnz, tw.row_ovf, plan.order, s,
                                list_by_order ? &late_list : nullptr, cls_part, n_cls_part));
