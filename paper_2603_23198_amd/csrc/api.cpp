@@ -658,7 +658,10 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   // rows the gather's first block builds it, with the token order a second workgroup of
   // the order kernel, else its own kernel
   OvfList late_list;
-  const bool token_order = bf && plan.order && nnz_token_order(*a);
+  // ELL rows too wide for the slice walk's LDS: token order over W_down itself (the walk over
+  // slice-major copies refuses them)
+  const bool wide_rows = !packed_gather(*a) && !slice_walk_fits(a->cfg.ell_width);
+  const bool token_order = bf && !wide_rows && plan.order && nnz_token_order(*a);
   const bool list_by_order = !list_by_gather(*a) && token_order;
   const int n_cls_part = cls_part ? (int)classify_grid(T, f, a->cfg.tile_cols) : 0;
   if (list_by_gather(*a) || list_by_order) {
@@ -693,7 +696,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   }
   // 3. sparse down projection of the ELL rows
   const void* WupT = a->W_upT;  // gated: W_up^T, given or built in the workspace when needed
-  if (bf) {
+  if (bf && !wide_rows) {
     const int32_t* order = nullptr;
     if (token_order) {
       // with a second workgroup building the dense-backup row list
@@ -747,8 +750,8 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
                                       form_h ? plan.part_u : nullptr, form_h ? a->stats : nullptr,
                                       list_by_order ? OvfList{} : late_list, row_major));
   } else {
-    SFL_HIP(launch_gather_down(T, d, a->cfg.ell_width, (const float*)tw.ell_val, tw.ell_idx, tw.row_nnz, tw.row_ovf,
-                               (const float*)a->W_down, (float*)a->Y, s, late_list));
+    SFL_HIP(launch_gather_down(vb, T, d, a->cfg.ell_width, tw.ell_val, tw.ell_idx, tw.row_nnz, tw.row_ovf, a->W_down,
+                               a->Y, s, late_list));
   }
   ev.record(3, s);
   // 4. dense-backup rows (Alg. 3, dense part), count on device: the dense ReLU rows are

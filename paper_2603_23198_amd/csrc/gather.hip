@@ -1,9 +1,9 @@
 // Sparse down projections from the compact ELL rows of the hybrid format.
 //
 // Non-gated (Alg. 3, sparse part): y[t, :] = sum_e v[t, e] * W_down[n[t, e], :].
-//  * k_gather_down (fp32, any d): (d-slice of 128 columns) x (block of tokens); a wave owns
-//    one token at a time and walks its ELL entries in order, reading one 512-byte W_down row
-//    segment per entry.
+//  * k_gather_down (fp32, any d; bf16 rows too wide for k_gather_down_b16's LDS): (d-slice of
+//    128 columns) x (block of tokens); a wave owns one token at a time and walks its ELL
+//    entries in order, reading the 128 columns of one W_down row per entry.
 //  * k_gather_down_b16 (bf16): over a slice-major copy of W_down (d % 512 == 0; other widths
 //    over W_down itself), each XCD walking its own 64-column slices so that one 2 MiB slice
 //    stays in its L2 while every token streams through it (see below). A work item is (slice, token), the 8 lane
@@ -53,13 +53,12 @@ __device__ __forceinline__ void ovf_list_small(int64_t T, const OvfList& ol, con
 // row's count are read, within the row's K, and not used), so that a row of up to 64 entries
 // waits for memory twice: its entries, then W. ODD: d is odd, the last lane of a row holds
 // one column.
-template <bool ODD>
-__global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K, const float* __restrict__ ell_val,
+template <typename V, bool ODD>
+__global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K, const V* __restrict__ ell_val,
                                                      const uint16_t* __restrict__ ell_idx,
                                                      const int32_t* __restrict__ row_nnz,
-                                                     const uint8_t* __restrict__ row_ovf, const float* __restrict__ W,
-                                                     float* __restrict__ Y, int n_slices, int n_tb, int tpw,
-                                                     OvfList ol) {
+                                                     const uint8_t* __restrict__ row_ovf, const V* __restrict__ W,
+                                                     V* __restrict__ Y, int n_slices, int n_tb, int tpw, OvfList ol) {
   if (ol.rows && blockIdx.x == 0 && threadIdx.x < 64) ovf_list_small(T, ol, row_ovf);
   const int g = blockIdx.x;
   int slice, tb;
@@ -79,19 +78,24 @@ __global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K
   const bool two = !ODD || col + 1 < d;
   auto load_w = [&](int64_t n) -> float2 {
     if (!col_ok) return make_float2(0.f, 0.f);
-    if (!two) return make_float2(W[n * d + col], 0.f);
-    return *(const float2*)(W + n * d + col);
+    if constexpr (sizeof(V) == 2) {
+      const uint32_t w = *(const uint32_t*)(W + n * d + col);
+      return make_float2(bf16lo(w), bf16hi(w));
+    } else {
+      if (!two) return make_float2(W[n * d + col], 0.f);
+      return *(const float2*)(W + n * d + col);
+    }
   };
   for (int tt = wave; tt < tpw; tt += 4) {
     const int64_t t = (int64_t)tb * tpw + tt;
     if (t >= T) break;
-    const float* ev = ell_val + t * (int64_t)K;
+    const V* ev = ell_val + t * (int64_t)K;
     const uint16_t* ei = ell_idx + t * (int64_t)K;
     const uint8_t ovf = row_ovf[t];
     const int cnt_t = row_nnz[t];
     const int l0 = min(l, max(K - 1, 0));
     int n_l = K > 0 ? (int)ei[l0] : 0;
-    float v_l = K > 0 ? ev[l0] : 0.f;
+    float v_l = K > 0 ? VT<V>::load(ev, l0) : 0.f;
     if (__builtin_amdgcn_readfirstlane((int)ovf)) continue;
     const int nnz = __builtin_amdgcn_readfirstlane(cnt_t);
     float a0 = 0.f, a1 = 0.f;
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K
       const int e = e0 + l;
       if (e0 > 0) {
         n_l = e < nnz ? (int)ei[e] : 0;
-        v_l = e < nnz ? ev[e] : 0.f;
+        v_l = e < nnz ? VT<V>::load(ev, e) : 0.f;
       }
       const int cnt = min(64, nnz - e0);
       int q = 0;
@@ -137,7 +141,9 @@ __global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K
       }
     }
     if (col_ok) {
-      if constexpr (ODD) {
+      if constexpr (sizeof(V) == 2) {
+        *(uint32_t*)(Y + t * d + col) = (uint32_t)f32_to_bf16(a0) | ((uint32_t)f32_to_bf16(a1) << 16);
+      } else if constexpr (ODD) {
         Y[t * d + col] = a0;
         if (two) Y[t * d + col + 1] = a1;
       } else {
@@ -1093,9 +1099,10 @@ static int slice_walk_tpw(int64_t T, int64_t per_tok);
 // least 1024 workgroups, fewer for smaller batches, down to one token per wave: the walk of a
 // token is a chain of loads, and 32 tokens at T = 64, d = 256 (4 workgroups) took 14.4 us,
 // 4 tokens (32 workgroups) 3.5 us.
-hipError_t launch_gather_down(int64_t T, int64_t d, int K, const float* ell_val, const uint16_t* ell_idx,
-                              const int32_t* row_nnz, const uint8_t* row_ovf, const float* W, float* Y, hipStream_t s,
+hipError_t launch_gather_down(int val_bf16, int64_t T, int64_t d, int K, const void* ell_val, const uint16_t* ell_idx,
+                              const int32_t* row_nnz, const uint8_t* row_ovf, const void* W, void* Y, hipStream_t s,
                               OvfList ol) {
+  if (val_bf16 && d % 2 != 0) return hipErrorInvalidValue;
   if (T == 0) return hipSuccess;
   if (ol.rows && (T > 64 || !ol.n)) return hipErrorInvalidValue;
   const int n_slices = (int)cdiv(d, SLICE);
@@ -1103,14 +1110,18 @@ hipError_t launch_gather_down(int64_t T, int64_t d, int K, const float* ell_val,
   while (tpw > 4 && cdiv(T, tpw) * n_slices < 1024) tpw /= 2;
   const int n_tb = (int)cdiv(T, tpw);
   const dim3 grid((unsigned)(n_slices * n_tb));
-  if (d % 2 == 0)
-    hipLaunchKernelGGL(k_gather_down<false>, grid, dim3(256), 0, s, T, d, K, ell_val, ell_idx, row_nnz, row_ovf, W, Y,
-                       n_slices, n_tb, tpw, ol);
-  else
-    hipLaunchKernelGGL(k_gather_down<true>, grid, dim3(256), 0, s, T, d, K, ell_val, ell_idx, row_nnz, row_ovf, W, Y,
-                       n_slices, n_tb, tpw, ol);
+#define SFL_GATHER_DOWN(V_, ODD_)                                                                              \
+  hipLaunchKernelGGL((k_gather_down<V_, ODD_>), grid, dim3(256), 0, s, T, d, K, (const V_*)ell_val, ell_idx, row_nnz, \
+                     row_ovf, (const V_*)W, (V_*)Y, n_slices, n_tb, tpw, ol)
+  if (val_bf16) SFL_GATHER_DOWN(bf16_t, false);
+  else if (d % 2 == 0) SFL_GATHER_DOWN(float, false);
+  else SFL_GATHER_DOWN(float, true);
+#undef SFL_GATHER_DOWN
   return hipGetLastError();
 }
+
+// A token's entries (4 bytes each) in a workgroup's LDS, 160 KB, with room to spare.
+bool slice_walk_fits(int K) { return K <= 32768; }
 
 hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int K, const void* ell_val,
                                      const uint16_t* ell_idx, const int32_t* row_nnz, const uint8_t* row_ovf,

@@ -208,11 +208,11 @@ struct OvfList {
   int32_t cap = 0;
   sfl_stats_t* stats = nullptr;
 };
-// fp32: Y[t, :] = sum_e ell_val[t][e] * W[ell_idx[t][e], :] for rows with row_ovf[t] == 0. With
+// Y[t, :] = sum_e ell_val[t][e] * W[ell_idx[t][e], :] for rows with row_ovf[t] == 0. With
 // ol.rows (at most 64 rows): block 0 also builds the dense-backup row list from row_ovf.
-hipError_t launch_gather_down(int64_t T, int64_t d, int ell_width, const float* ell_val, const uint16_t* ell_idx,
-                              const int32_t* row_nnz, const uint8_t* row_ovf, const float* W, float* Y, hipStream_t s,
-                              OvfList ol = OvfList());
+hipError_t launch_gather_down(int val_bf16, int64_t T, int64_t d, int ell_width, const void* ell_val,
+                              const uint16_t* ell_idx, const int32_t* row_nnz, const uint8_t* row_ovf, const void* W,
+                              void* Y, hipStream_t s, OvfList ol = OvfList());
 // order[0 .. T): the sparse rows by descending row_nnz, then the dense-backup rows (one
 // workgroup, counting sort over K + 2 buckets; order within a bucket unspecified; with
 // row_ovf null every row counts as sparse and counts above K share the first bucket).
@@ -225,7 +225,9 @@ hipError_t launch_nnz_order(int64_t T, int K, const int32_t* row_nnz, const uint
                             hipStream_t s, const OvfList* list = nullptr, const ClassifyPart* parts = nullptr,
                             int n_parts = 0);
 // bf16, d % 512 == 0: same sum from the slice-major copy of W_down (XCD-aware); row_major
-// (d % 64 == 0; bf16 values, out_mode 0): from W_down [f][d] itself.
+// (d % 64 == 0; bf16 values, out_mode 0): from W_down [f][d] itself. ELL rows up to
+// slice_walk_fits wide.
+bool slice_walk_fits(int ell_width);
 // out_mode 0: bf16 Y; 1: fp32 Yf; 2: bf16 Y of (sum + Yf) (val_f32 only for 1 and 2).
 // With ol.rows (at most 64 rows): block 0 also builds the dense-backup row list from row_ovf
 // (as launch_ovf_list would), before anything else.

@@ -480,6 +480,29 @@ def test_widths_not_a_multiple_of_512(T, d, f, K):
         assert np.linalg.norm(Yg[t] - Yref[t]) <= 2e-2 * np.linalg.norm(Yref[t]), t
 
 
+@pytest.mark.parametrize("T,K", [(3, 32768), (3, 32769), (2, 50000), (70, 50000), (258, 50000)])
+def test_widest_ell_rows(T, K):
+    """ELL rows on both sides of what a workgroup's LDS holds, at a width that is not a multiple
+    of 512: every row stays on the sparse path and Y is the oracle's."""
+    w = wl.make_ffn("widest rows", "bf16", T, 64, 65472, seed=K + T, sparsity=0.5, tile_cols=256, tile_slots=256,
+                    ell_width=K)
+    w.shift_t[:] = 0.03 if K == 50000 else -0.03  # about 58 and 42 % active
+    Y, bufs, _, cfg = run_forward(w, use_wupt=T % 2 == 0)
+    Yref, _ = oracle_rows(w, np.arange(T))
+    assert host_bits(bufs["row_ovf"])[:T].sum() == 0
+    assert rel_l2(to_f64(Y), Yref) <= 2e-2
+
+
+@pytest.mark.parametrize("f", [576, 1984])
+def test_gated_without_copies_equals_given_slices(f):
+    """W_up's slice-major copy made inside the call (f an odd number of 64-column tiles) gives
+    the bits of one that the caller packed from the transpose."""
+    w = wl.make_ffn("slices", "bf16", 300, 512, f, seed=f, sparsity=0.95, gated=True, ell_width=192, tile_slots=64)
+    w.shift_t[::17] = 50.0
+    Y0, Y1 = run_forward(w)[0], run_forward(w, packed_up=True)[0]
+    np.testing.assert_array_equal(host_bits(Y0), host_bits(Y1))
+
+
 def test_all_active_and_all_inactive_rows():
     w = wl.make_ffn("extremes", "bf16", 96, 256, 512, seed=3, sparsity=0.95, ell_width=32)
     w.shift_t[:8] = 100.0     # every unit active -> dense-backup rows
