@@ -1413,12 +1413,14 @@ hipError_t launch_twell(const GemmParams& p, hipStream_t s) {
 // forward at T = 512, d = 1024, f = 4096 went 246 -> 78 us.
 // LDS rows are padded by 4 floats: A's [m][k] rows are then read 16 bytes (four k) per lane
 // and B's [k][n] rows 4 bytes per lane without bank conflicts. The MFMA j of a 16-k group
-// takes k = 4 (lane / 16) + j of both operands.
+// takes k = 4 (lane / 16) + j of both operands. Each output is the sum of two or four partial
+// sums: the MFMAs of one depend on each other, and shorter sums round less.
 template <int BT> struct F32Geo {
   static constexpr int BKF = BT == 64 ? 64 : 128;      // k per step
   static constexpr int LDA = BKF + 4, LDB = BT + 4;    // padded LDS row lengths
   static constexpr int CA = BT * BKF / 4 / 256;        // 16-byte chunks per thread (same for B)
   static constexpr int NB = BT / 32;                   // 16 x 16 blocks per wave and dimension
+  static constexpr int NCH = BT == 64 ? 2 : 4;         // partial sums per output, over k mod 4
 };
 
 // VEC: K and N multiples of 4 and 16-byte aligned operands (else element-wise loads).
@@ -1465,11 +1467,13 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmParams p) {
       rb[u] = vb;
     }
   };
-  f32x4_t acc[G::NB][G::NB];
+  f32x4_t sum[G::NCH][G::NB][G::NB];
 #pragma unroll
-  for (int i = 0; i < G::NB; ++i)
+  for (int h = 0; h < G::NCH; ++h)
 #pragma unroll
-    for (int j = 0; j < G::NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < G::NB; ++i)
+#pragma unroll
+      for (int j = 0; j < G::NB; ++j) sum[h][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int wm = (wave & 1) * (BT / 2), wn = (wave >> 1) * (BT / 2);
   fetch(0);
   for (int k0 = 0; k0 < p.K; k0 += G::BKF) {
@@ -1496,11 +1500,20 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmParams p) {
         for (int i = 0; i < G::NB; ++i)
 #pragma unroll
           for (int j = 0; j < G::NB; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j], acc[i][j], 0, 0, 0);
+            sum[e % G::NCH][i][j] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j], sum[e % G::NCH][i][j], 0, 0, 0);
       }
     }
     __syncthreads();
   }
+  f32x4_t acc[G::NB][G::NB];
+#pragma unroll
+  for (int i = 0; i < G::NB; ++i)
+#pragma unroll
+    for (int j = 0; j < G::NB; ++j) {
+      acc[i][j] = sum[0][i][j] + sum[1][i][j];
+      if constexpr (G::NCH == 4) acc[i][j] += sum[2][i][j] + sum[3][i][j];
+    }
   float l1 = 0.f;
 #pragma unroll
   for (int i = 0; i < G::NB; ++i)
