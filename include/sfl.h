@@ -204,7 +204,7 @@ typedef struct {
  *            [d/64][f][64] with element [s][n][c] = W_up[64 s + c][n], i.e.
  *            sfl_pack_down_weights applied to W_up^T. The gated up-dots read 64-row
  *            slices of W_up; when NULL the forward builds it in the workspace on every
- *            call (from W_upT, itself transposed into the workspace when NULL).
+ *            call (from W_upT, or from W_up when that is NULL).
  *  bias_f    optional float32 [f] added to every pre-activation of column n
  *  shift_t   optional float32 [T] added to every pre-activation of row t
  *            (both are extensions; NULL/NULL is the paper's bias-free FFN)
