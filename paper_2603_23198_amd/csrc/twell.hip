@@ -9,6 +9,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace sfl {
 
@@ -611,19 +612,22 @@ hipError_t launch_pack_classify_rows(const float* Z, int ks, const float* bias, 
 // with kPackRowsUnroll loads in flight, and the slabs are not read back. A step is 256
 // consecutive columns, four per lane (as in k_pack_classify_rows): a TwELL tile is T_n / 4
 // lanes, the ballots below a lane in its tile give the slot, those below it in the wave, after
-// the quarter's entries so far, its place among the quarter's ELL entries. These wait in LDS
-// for the row's total (a dense-backup row's are not written) and the counts of the quarters
-// before. Bound by the latency of reading Z: T = 4001, f = 5600 (90 MB) takes about 33 us (one
-// wave per row: 39; one wave per (row, tile) at 4 bytes per lane 32, then the classification 12).
+// the quarter's entries so far, its place among the quarter's entries. These wait in LDS for
+// the row's total and the counts of the quarters before, and then go to the slabs and (unless
+// the row is a dense-backup one) to the ELL row 64 per store: stored as they are found, each
+// register of four columns took its own nearly empty store instructions. A quarter of more
+// than K entries, necessarily of a dense-backup row, is walked again to store its slabs. Two
+// blocks per CU (at most 64 VGPRs and 96 SGPRs). T = 4001, f = 5600 (90 MB of Z): the entry
+// point 57.0 us with one wave per (row, tile) and a classification of its own, 41.6 with the
+// entries stored as found, 35.0 now.
 constexpr int kPackRowsWaves = 16;                   // per block
 constexpr int kPackRowsParts = 4;                    // waves per row
 constexpr int kPackRowsUnroll = 6;
 constexpr int kPackRowsPerBlock = kPackRowsWaves / kPackRowsParts;
-constexpr size_t kPackRowsLds = 64 * 1024;
-constexpr uint32_t kPackNoStore = 0x80000000u;       // an offset past every slab
+constexpr size_t kPackRowsLds = 79 * 1024;           // two blocks per CU
 
 template <typename V, bool PK, int TN>
-__global__ __launch_bounds__(kPackRowsWaves * 64) void k_pack_rows(
+__global__ __launch_bounds__(kPackRowsWaves * 64, 8) void k_pack_rows(
     const float* __restrict__ Z, int64_t T, int f, int S, int NT, int K, V* __restrict__ val,
     uint16_t* __restrict__ idx, int32_t* __restrict__ cnt, int32_t* __restrict__ row_nnz, uint8_t* __restrict__ row_ovf,
     V* __restrict__ ell_val, uint16_t* __restrict__ ell_idx, sfl_stats_t* __restrict__ stats, int l1_vals) {
@@ -631,9 +635,11 @@ __global__ __launch_bounds__(kPackRowsWaves * 64) void k_pack_rows(
   __shared__ int w_cnt[2][kPackRowsWaves], w_over[2][kPackRowsWaves];  // by turns, one pass after the other
   const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int part = w % kPackRowsParts;
-  // [waves][K + 1] values, [waves][K + 1] columns; entries that are not kept go to place K
-  V* const ev = (V*)pr_lds + (size_t)w * (K + 1);
-  uint16_t* const ec = (uint16_t*)((V*)pr_lds + (size_t)kPackRowsWaves * (K + 1)) + (size_t)w * (K + 1);
+  // [waves][K] values, columns and slots of the quarter's entries
+  const size_t n_lds = (size_t)kPackRowsWaves * K;
+  V* const ev = (V*)pr_lds + (size_t)w * K;
+  uint16_t* const ec = (uint16_t*)((V*)pr_lds + n_lds) + (size_t)w * K;
+  uint8_t* const es = (uint8_t*)((uint16_t*)((V*)pr_lds + n_lds) + n_lds) + (size_t)w * K;
   constexpr int GL = TN / 4;  // lanes per TwELL tile
   const int gsh = l & ~(GL - 1);
   const uint64_t gbits = GL == 64 ? ~0ull : (1ull << GL) - 1ull;
@@ -648,16 +654,23 @@ __global__ __launch_bounds__(kPackRowsWaves * 64) void k_pack_rows(
   for (int64_t t0 = (int64_t)blockIdx.x * kPackRowsPerBlock; t0 < T; t0 += (int64_t)gridDim.x * kPackRowsPerBlock) {
     const int64_t t = t0 + w / kPackRowsParts;
     int mine = 0, over = 0;
-    if (t < T) {
+    // one entry of the row's slabs
+    auto store_slot = [&](int col, int slot, V v) {
+      const int64_t tile = (uint32_t)col / TN, at = t * row_words + (PK ? tile * 32 + 1 : tile * S) + slot;
+      if constexpr (PK) {
+        ((uint32_t*)val)[at] = (uint32_t)col | ((uint32_t)v << 16);
+      } else {
+        val[at] = v;
+        idx[at] = (uint16_t)col;
+      }
+    };
+    // the quarter's columns: its entries into LDS (as many as fit) and its tiles' counts to
+    // memory, or, with DIRECT, its entries to the slabs
+    auto walk = [&](auto direct) {
+      constexpr bool DIRECT = decltype(direct)::value;
       const float* zr = Z + t * f;
-      // the row's slabs: stores at an offset past a slab's end (lanes without an entry, slots
-      // from S on) write nothing
-      constexpr int es = PK ? 4 : (int)sizeof(V);
-      const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
-          (void*)((char*)val + t * row_words * es), (short)0, (int)(row_words * es), 0x00020000);
-      const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc(
-          PK ? (void*)val : (void*)(idx + t * row_words), (short)0, (int)(row_words * 2), 0x00020000);
-      int32_t* const rc = PK ? nullptr : cnt + t * NT;
+      mine = 0;
+      over = 0;
       for (int c0 = c_lo; c0 < c_hi; c0 += 256 * kPackRowsUnroll) {
         float4 z[kPackRowsUnroll];  // columns past the row re-read its last four and are not active
 #pragma unroll
@@ -691,34 +704,30 @@ __global__ __launch_bounds__(kPackRowsWaves * 64) void k_pack_rows(
           for (int r = 0; r < 4; ++r) {
             if (m[r] == 0) continue;  // uniform
             const bool act = in && is_active(zz[r]);
-            const uint16_t c16 = (uint16_t)(col + r);
-            const V v = VT<V>::cvt(zz[r]);
-            const uint32_t at = (uint32_t)(PK ? j * 32 + 1 + slot : j * S + slot);
-            const bool st = act && slot < S;
-            if constexpr (PK) {
-              __builtin_amdgcn_raw_buffer_store_b32((uint32_t)c16 | ((uint32_t)v << 16), rv, st ? at * 4u : kPackNoStore,
-                                                    0, 0);
-            } else {
-              if constexpr (sizeof(V) == 2)
-                __builtin_amdgcn_raw_buffer_store_b16(v, rv, st ? at * 2u : kPackNoStore, 0, 0);
-              else
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rv, st ? at * 4u : kPackNoStore, 0, 0);
-              __builtin_amdgcn_raw_buffer_store_b16(c16, ri, st ? at * 2u : kPackNoStore, 0, 0);
+            if (act) {
+              if constexpr (DIRECT) {
+                if (slot < S) store_slot(col + r, slot, VT<V>::cvt(zz[r]));
+              } else if (pos < K) {
+                ev[pos] = VT<V>::cvt(zz[r]);
+                ec[pos] = (uint16_t)(col + r);
+                es[pos] = (uint8_t)slot;  // below T_n
+              }
             }
-            const int place = act ? min(pos, K) : K;
-            ev[place] = v;
-            ec[place] = c16;
             slot += act ? 1 : 0;
             pos += act ? 1 : 0;
           }
           const bool first = in && l == gsh;
-          if (first) {
-            if constexpr (PK) __builtin_amdgcn_raw_buffer_store_b32((uint32_t)cnt_tile, rv, (uint32_t)j * 128u, 0, 0);
-            else rc[(uint32_t)j] = cnt_tile;
+          if (!DIRECT && first) {
+            if constexpr (PK) ((uint32_t*)val)[t * row_words + j * 32] = (uint32_t)cnt_tile;
+            else cnt[t * NT + j] = cnt_tile;
           }
           over += __popcll(ballot(first && cnt_tile > S));
         }
       }
+    };
+    if (t < T) {
+      walk(std::false_type{});
+      if (mine > K) walk(std::true_type{});  // uniform
     }
     if (l == 0) {
       w_cnt[turn][w] = mine;
@@ -745,13 +754,17 @@ __global__ __launch_bounds__(kPackRowsWaves * 64) void k_pack_rows(
       nnz_sum += total;
       over_sum += over;
     }
-    if (!ovf && keep) {
+    if (mine <= K) {
+      const bool ell = !ovf && keep;
       for (int e = l; e < mine; e += 64) {
         const V v = ev[e];
-        if (l1_vals) l1 += VT<V>::load(&v, 0);
-        if (ell_val) {
+        const uint16_t c = ec[e];
+        const int slot = es[e];
+        if (slot < S) store_slot(c, slot, v);
+        if (ell && l1_vals) l1 += VT<V>::load(&v, 0);
+        if (ell && ell_val) {
           ell_val[t * (int64_t)K + before + e] = v;
-          ell_idx[t * (int64_t)K + before + e] = ec[e];
+          ell_idx[t * (int64_t)K + before + e] = c;
         }
       }
     }
@@ -766,7 +779,7 @@ __global__ __launch_bounds__(kPackRowsWaves * 64) void k_pack_rows(
 bool pack_rows_ok(int64_t T, int64_t f, int Tn, int K, int val_bf16) {
   if (T <= kRowPackMaxRows || f % 4 != 0 || f < 4 || f > 65535) return false;
   if (Tn != 64 && Tn != 128 && Tn != 256) return false;
-  return (size_t)kPackRowsWaves * (K + 1) * (2 + (val_bf16 ? 2 : 4)) <= kPackRowsLds;
+  return (size_t)kPackRowsWaves * K * (3 + (val_bf16 ? 2 : 4)) <= kPackRowsLds;
 }
 
 hipError_t launch_pack_rows(const float* Z, int64_t T, int64_t f, int val_bf16, int Tn, int S, int K, void* val,
@@ -775,17 +788,22 @@ hipError_t launch_pack_rows(const float* Z, int64_t T, int64_t f, int val_bf16, 
   if (!pack_rows_ok(T, f, Tn, K, val_bf16) || ((uintptr_t)Z & 15)) return hipErrorInvalidValue;
   if (packed && (!val_bf16 || S != 31)) return hipErrorInvalidValue;
   const int NT = (int)cdiv(f, Tn);
-  const size_t lds = (size_t)kPackRowsWaves * (K + 1) * (2 + (val_bf16 ? 2 : 4));
+  const size_t lds = (size_t)kPackRowsWaves * K * (3 + (val_bf16 ? 2 : 4));
   // at most 512 blocks (two per CU): their statistics are added by same-address atomics
   const dim3 grid((unsigned)std::min<int64_t>(cdiv(T, kPackRowsPerBlock), 512)), block(kPackRowsWaves * 64);
 #define SFL_PACK_ROWS_TN(V_, PK_, TN_)                                                                            \
+  if (lds > 65536) {                                                                                              \
+    const hipError_t e = hipFuncSetAttribute((const void*)k_pack_rows<V_, PK_, TN_>,                              \
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);               \
+    if (e != hipSuccess) return e;                                                                                \
+  }                                                                                                               \
   hipLaunchKernelGGL((k_pack_rows<V_, PK_, TN_>), grid, block, lds, s, Z, T, (int)f, S, NT, K, (V_*)val, idx, cnt, \
                      row_nnz, row_ovf, (V_*)ell_val, ell_idx, stats, l1_vals)
-#define SFL_PACK_ROWS(V_, PK_)                      \
-  do {                                              \
-    if (Tn == 256) SFL_PACK_ROWS_TN(V_, PK_, 256);  \
-    else if (Tn == 128) SFL_PACK_ROWS_TN(V_, PK_, 128); \
-    else SFL_PACK_ROWS_TN(V_, PK_, 64);             \
+#define SFL_PACK_ROWS(V_, PK_)                          \
+  do {                                                  \
+    if (Tn == 256) { SFL_PACK_ROWS_TN(V_, PK_, 256); }  \
+    else if (Tn == 128) { SFL_PACK_ROWS_TN(V_, PK_, 128); } \
+    else { SFL_PACK_ROWS_TN(V_, PK_, 64); }             \
   } while (0)
   if (packed) SFL_PACK_ROWS(bf16_t, true);
   else if (val_bf16) SFL_PACK_ROWS(bf16_t, false);
