@@ -163,9 +163,9 @@ hipError_t launch_pack_classify_rows(const float* Z, int ks, const float* bias, 
                                      uint16_t* idx, int32_t* cnt, int32_t* row_nnz, uint8_t* row_ovf, void* ell_val,
                                      uint16_t* ell_idx, sfl_stats_t* stats, hipStream_t s, int l1_vals = 1,
                                      bool packed = false);
-// Batches of more than 256 rows with f a multiple of 4, T_n of 64, 128 or 256 and ELL rows
+// Batches of more than 256 rows with f above 768 and a multiple of 4, T_n of 64, 128 or 256 and ELL rows
 // that fit the kernel's LDS: the pack from Z (16-byte aligned) and the classification in one
-// launch, one wave per row. The outputs and statistics are those of the two launches.
+// launch, four waves per row. The outputs and statistics are those of the two launches.
 bool pack_rows_ok(int64_t T, int64_t f, int tile_cols, int ell_width, int val_bf16);
 hipError_t launch_pack_rows(const float* Z, int64_t T, int64_t f, int val_bf16, int tile_cols, int tile_slots,
                             int ell_width, void* val, uint16_t* idx, int32_t* cnt, int32_t* row_nnz, uint8_t* row_ovf,

@@ -48,6 +48,8 @@ CASES = [
     (700, 1284, 128, 16, 60, 9, "f32"),      # partial last step, capacity below the overflow rows
     (513, 1024, 64, 8, 0, 0, "bf16"),        # every active row is a dense-backup row
     (8300, 132, 64, 12, 12, 0, "f32"),       # more rows than waves
+    (300, 768, 256, 16, 40, 0, "bf16"),      # pack and classification apart
+    (300, 772, 256, 16, 40, 0, "bf16"),      # the fourth wave with one lane of columns
     (300, 8192, 256, 32, 1011, 0, "bf16"),   # the widest ELL rows the waves' LDS holds
     (300, 8192, 256, 32, 1012, 0, "bf16"),   # wider: pack and classification apart
     (300, 8192, 128, 32, 722, 0, "f32"),     # the widest in float32
