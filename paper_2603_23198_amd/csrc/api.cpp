@@ -658,10 +658,10 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   // rows the gather's first block builds it, with the token order a second workgroup of
   // the order kernel, else its own kernel
   OvfList late_list;
-  // ELL rows too wide for the slice walk's LDS: token order over W_down itself (the walk over
-  // slice-major copies refuses them)
-  const bool wide_rows = !packed_gather(*a) && !slice_walk_fits(a->cfg.ell_width);
-  const bool token_order = bf && !wide_rows && plan.order && nnz_token_order(*a);
+  // the slice walk (bf16: over slice-major copies or, at other widths, over W_down itself), or
+  // the plain gather in token order
+  const bool slice_walk = bf && (packed_gather(*a) || row_major_walk_ok(d, a->cfg.ell_width));
+  const bool token_order = slice_walk && plan.order && nnz_token_order(*a);
   const bool list_by_order = !list_by_gather(*a) && token_order;
   const int n_cls_part = cls_part ? (int)classify_grid(T, f, a->cfg.tile_cols) : 0;
   if (list_by_gather(*a) || list_by_order) {
@@ -696,7 +696,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   }
   // 3. sparse down projection of the ELL rows
   const void* WupT = a->W_upT;  // gated: W_up^T, given or built in the workspace when needed
-  if (bf && !wide_rows) {
+  if (slice_walk) {
     const int32_t* order = nullptr;
     if (token_order) {
       // with a second workgroup building the dense-backup row list

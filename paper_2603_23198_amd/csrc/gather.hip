@@ -1,7 +1,7 @@
 // Sparse down projections from the compact ELL rows of the hybrid format.
 //
 // Non-gated (Alg. 3, sparse part): y[t, :] = sum_e v[t, e] * W_down[n[t, e], :].
-//  * k_gather_down (fp32, any d; bf16 rows too wide for k_gather_down_b16's LDS): (d-slice of
+//  * k_gather_down (fp32, any d; bf16 rows that row_major_walk_ok leaves to it): (d-slice of
 //    128 columns) x (block of tokens); a wave owns one token at a time and walks its ELL
 //    entries in order, reading the 128 columns of one W_down row per entry.
 //  * k_gather_down_b16 (bf16): over a slice-major copy of W_down (d % 512 == 0; other widths
@@ -1120,8 +1120,10 @@ hipError_t launch_gather_down(int val_bf16, int64_t T, int64_t d, int K, const v
   return hipGetLastError();
 }
 
-// A token's entries (4 bytes each) in a workgroup's LDS, 160 KB, with room to spare.
-bool slice_walk_fits(int K) { return K <= 32768; }
+// Whether the row-major walk takes rows of K entries at width d: a token's entries (4 bytes
+// each) in a workgroup's LDS, 160 KB, with room to spare, and the byte stride of a W_down row
+// in the 24 bits of slice_token's multiply.
+bool row_major_walk_ok(int64_t d, int K) { return K <= 32768 && d < (int64_t)1 << 23; }
 
 hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int K, const void* ell_val,
                                      const uint16_t* ell_idx, const int32_t* row_nnz, const uint8_t* row_ovf,
@@ -1131,7 +1133,8 @@ hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int K, con
   if (T == 0) return hipSuccess;
   if (ol.rows && (T > 64 || !ol.n)) return hipErrorInvalidValue;
   if (part_u && (val_f32 || out_mode != 0)) return hipErrorInvalidValue;
-  if (row_major && (val_f32 || out_mode != 0 || part_u || f * d * 2 >= (int64_t)1 << 31)) return hipErrorInvalidValue;
+  if (row_major && (val_f32 || out_mode != 0 || part_u || f * d * 2 >= (int64_t)1 << 31 || !row_major_walk_ok(d, K)))
+    return hipErrorInvalidValue;
   if (d % (row_major ? SLICE2 : 8 * SLICE2) != 0) return hipErrorInvalidValue;
   if (out_mode < 0 || out_mode > 2 || (out_mode > 0 && !Yf) || (out_mode != 1 && !Y)) return hipErrorInvalidValue;
   const int n_slices = (int)(d / SLICE2);

@@ -225,9 +225,8 @@ hipError_t launch_nnz_order(int64_t T, int K, const int32_t* row_nnz, const uint
                             hipStream_t s, const OvfList* list = nullptr, const ClassifyPart* parts = nullptr,
                             int n_parts = 0);
 // bf16, d % 512 == 0: same sum from the slice-major copy of W_down (XCD-aware); row_major
-// (d % 64 == 0; bf16 values, out_mode 0): from W_down [f][d] itself. ELL rows up to
-// slice_walk_fits wide.
-bool slice_walk_fits(int ell_width);
+// (d % 64 == 0; bf16 values, out_mode 0; row_major_walk_ok): from W_down [f][d] itself.
+bool row_major_walk_ok(int64_t d, int ell_width);
 // out_mode 0: bf16 Y; 1: fp32 Yf; 2: bf16 Y of (sum + Yf) (val_f32 only for 1 and 2).
 // With ol.rows (at most 64 rows): block 0 also builds the dense-backup row list from row_ovf
 // (as launch_ovf_list would), before anything else.

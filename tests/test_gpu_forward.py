@@ -480,6 +480,24 @@ def test_widths_not_a_multiple_of_512(T, d, f, K):
         assert np.linalg.norm(Yg[t] - Yref[t]) <= 2e-2 * np.linalg.norm(Yref[t]), t
 
 
+def test_row_stride_past_24_bits():
+    """A width whose W_down rows are 2^24 bytes apart or more (so f = 64): the sampled columns
+    of every row against the float64 product over the active units, half of them."""
+    T, d, f = 3, 2 ** 23 + 64, 64
+    g = torch.Generator(device="cuda").manual_seed(24)
+    rand = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    X, Wu, Wd = rand(T, d).bfloat16(), (rand(d, f) * 0.02).bfloat16(), (rand(f, d) * 0.02).bfloat16()
+    cfg = b.make_cfg(tile_cols=64, tile_slots=64, ell_width=64, ovf_capacity=1)
+    bufs, Y = b.alloc_twell(T, f, "bf16", cfg), torch.full((T, d), float("nan"), dtype=X.dtype, device="cuda")
+    kw = dict(Y=Y, bufs=bufs)
+    ws = torch.empty(b.sfl_workspace_size(b.ffn_args(X, Wu, Wd, cfg, **kw)), dtype=torch.uint8, device="cuda")
+    b.sfl_ffn_forward(b.ffn_args(X, Wu, Wd, cfg, workspace=ws, **kw))
+    H = (X.double() @ Wu.double()).clamp_(min=0)
+    cols = torch.cat([torch.arange(0, d, 65537), torch.arange(d - 128, d)]).cuda()
+    Yref = H @ Wd[:, cols].double()
+    assert rel_l2(to_f64(Y[:, cols]), to_f64(Yref)) <= 2e-2
+
+
 @pytest.mark.parametrize("T,K", [(3, 32768), (3, 32769), (2, 50000), (70, 50000), (258, 50000)])
 def test_widest_ell_rows(T, K):
     """ELL rows on both sides of what a workgroup's LDS holds, at a width that is not a multiple
