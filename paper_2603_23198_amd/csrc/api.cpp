@@ -152,7 +152,7 @@ sfl_status_t check_twell(const sfl_twell_t& t, bool need_ell, int64_t T, bool pa
 struct FwdPlan {
   float* Z = nullptr;        // unfused path: fp32 pre-activations [T][f]
   void* ovf_dense = nullptr; // dense-backup rows when the caller gave none [cap][f]
-  void* WupT = nullptr;      // gated: W_up transposed [f][d]
+  void* WupT = nullptr;      // gated: W_up transposed [f][d], where it is not packed straight from W_up
   void* WdP = nullptr;       // slice-major W_down when the caller gave none [d/64][f][64]
   void* WuP = nullptr;       // gated: slice-major W_up when the caller gave none [d/64][f][64]
   float* part_u = nullptr;   // gated: per-XCD partial up-dots [8][T][K]
@@ -719,7 +719,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
       if (!WuP) {
         // straight from W_up, unless the dense-backup rows' GEMMs read W_gate^T (and then
         // W_up^T beside it)
-        if (!WupT && !a->W_gateT && pack_transposed_ok(a->W_up, d, f)) {
+        if (!WupT && !a->W_gateT && pack_transposed_ok(a->W_up, plan.WuP, d, f)) {
           SFL_HIP(launch_pack_transposed(a->W_up, plan.WuP, d, f, s));
         } else {
           if (!WupT) {

@@ -296,8 +296,10 @@ struct BwdPlan {
   u32x4_t* csc_rec = nullptr; // [T K] records: token, h, dz (gated: dh_u), gated: dh_g
   float* dWuT = nullptr;      // [f][d]
   float* dWgT = nullptr;      // gated: [f][d]
-  void* WupT = nullptr;       // [f][d] when neither W_upT nor W_up_packed is given
-  void* WgT = nullptr;        // gated: [f][d] when neither W_gateT nor W_gate_packed is given
+  // room for transposes when neither copy is given; used where pack_transposed_ok does not hold
+  // (the sizes are asked for before the workspace's alignment is known)
+  void* WupT = nullptr;       // [f][d] without W_upT and W_up_packed
+  void* WgT = nullptr;        // gated: [f][d] without W_gateT and W_gate_packed
   void* WdP = nullptr;        // slice-major W_down when not given
   void* WuP = nullptr;        // slice-major W_up^T when not given
   void* WgP = nullptr;        // gated: slice-major W_gate^T when not given
@@ -446,7 +448,7 @@ sfl_status_t backward_run(const sfl_ffn_bwd_args_t* a, hipStream_t s) {
     }
     *res = out;
     if (given_T) return launch_pack_down(given_T, out, f, d, s);
-    if (pack_transposed_ok(W, d, f)) return launch_pack_transposed(W, out, d, f, s);
+    if (pack_transposed_ok(W, out, d, f)) return launch_pack_transposed(W, out, d, f, s);
     const hipError_t e = launch_transpose(W, tmpT, d, f, 2, s);
     return e != hipSuccess ? e : launch_pack_down(tmpT, out, f, d, s);
   };

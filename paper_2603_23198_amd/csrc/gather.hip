@@ -1332,13 +1332,13 @@ hipError_t launch_gated_h(int64_t T, int K, const void* ell_val, const int32_t* 
   return hipGetLastError();
 }
 
-bool pack_transposed_ok(const void* W, int64_t d, int64_t f) {
+bool pack_transposed_ok(const void* W, const void* out, int64_t d, int64_t f) {
   static_assert(SLICE2 == 64, "64 x 64 tiles");
-  return d % 64 == 0 && f % 64 == 0 && ((uintptr_t)W & 15) == 0 && d / 64 <= 65535;
+  return d % 64 == 0 && f % 64 == 0 && (((uintptr_t)W | (uintptr_t)out) & 15) == 0 && d / 64 <= 65535;
 }
 
 hipError_t launch_pack_transposed(const void* W, void* out, int64_t d, int64_t f, hipStream_t s) {
-  if (!pack_transposed_ok(W, d, f) || ((uintptr_t)out & 15)) return hipErrorInvalidValue;
+  if (!pack_transposed_ok(W, out, d, f)) return hipErrorInvalidValue;
   if (d == 0 || f == 0) return hipSuccess;
   hipLaunchKernelGGL(k_pack_transposed, dim3((unsigned)(f / 64), (unsigned)(d / 64)), dim3(256), 0, s,
                      (const bf16_t*)W, (bf16_t*)out, f);

@@ -244,9 +244,9 @@ hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int ell_wi
 hipError_t launch_gated_entry_grads(int64_t T, int K, const void* ell_val, const int32_t* row_nnz,
                                     const uint8_t* row_ovf, const float* part, const float* u, float lam, float* dhu,
                                     float* dhg, float* h, hipStream_t s);
-// Slice-major copy of W^T from W [d][f] (bf16; d, f multiples of 64, 16-byte aligned), as
-// launch_pack_down gives it from W^T.
-bool pack_transposed_ok(const void* W, int64_t d, int64_t f);
+// Slice-major copy of W^T from W [d][f] (bf16; d, f multiples of 64, both 16-byte aligned: a
+// caller's workspace need not be), as launch_pack_down gives it from W^T.
+bool pack_transposed_ok(const void* W, const void* out, int64_t d, int64_t f);
 hipError_t launch_pack_transposed(const void* W, void* out, int64_t d, int64_t f, hipStream_t s);
 hipError_t launch_pack_down(const void* W, void* out, int64_t f, int64_t d, hipStream_t s);
 // Gated, two passes over slice-major copies: per-XCD partial up-dots u of every ELL entry

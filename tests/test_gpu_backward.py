@@ -206,7 +206,7 @@ def test_backward_c5_sampled():
 
 # ---- gated block (eq. sec3:eq:all_other_gradients with eq. l1 on h = ReLU(g) h_u) --------
 
-def run_gated_fwd_bwd(w, lam, copies=False):
+def run_gated_fwd_bwd(w, lam, copies=False, ws_offset=0):
     X, Wg, Wu, Wd, dY = dev(w.X), dev(w.W_gate), dev(w.W_up), dev(w.W_down), dev(w.dY)
     cfg = b.make_cfg(**w.cfg)
     bufs = b.alloc_twell(w.T, w.f, "bf16", cfg)
@@ -234,7 +234,7 @@ def run_gated_fwd_bwd(w, lam, copies=False):
         extra["W_gate_packed"] = pk(extra["W_gateT"])
     bkw = dict(W_gate=Wg, dW_gate=dWg, bias_f=dev(w.bias_f), shift_t=dev(w.shift_t), **extra)
     ba = b.bwd_args(X, Wu, Wd, dY, cfg, bufs, lam, dX, dWu, dWd, **bkw)
-    bws = torch.empty(max(1, b.sfl_workspace_size(ba, 1)), dtype=torch.uint8, device="cuda")
+    bws = torch.empty(max(1, b.sfl_workspace_size(ba, 1)) + ws_offset, dtype=torch.uint8, device="cuda")[ws_offset:]
     b.sfl_ffn_backward(b.bwd_args(X, Wu, Wd, dY, cfg, bufs, lam, dX, dWu, dWd, workspace=bws, **bkw))
     torch.cuda.synchronize()
     return dX, dWg, dWu, dWd, bufs, cfg
@@ -281,6 +281,13 @@ def test_gated_backward_copies_and_determinism():
         for x, y in zip(a[:4], other[:4]):
             assert torch.equal(x.view(torch.int16) if x.dtype == torch.bfloat16 else x.view(torch.int32),
                                y.view(torch.int16) if y.dtype == torch.bfloat16 else y.view(torch.int32))
+
+
+def test_gated_backward_workspace_on_an_8_byte_boundary():
+    """Without weight copies the slice-major ones are made in a workspace of any alignment."""
+    w = wl.make_ffn("gboff", "bf16", 200, 512, 1088, seed=37, gated=True, sparsity=0.98, ell_width=96, with_dy=True)
+    for x, y in zip(run_gated_fwd_bwd(w, 2e-5)[:4], run_gated_fwd_bwd(w, 2e-5, ws_offset=8)[:4]):
+        np.testing.assert_array_equal(host_bits(x), host_bits(y))
 
 
 def test_backward_c5_bench_configuration_is_identical():

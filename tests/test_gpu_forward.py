@@ -521,6 +521,26 @@ def test_gated_without_copies_equals_given_slices(f):
     np.testing.assert_array_equal(host_bits(Y0), host_bits(Y1))
 
 
+@pytest.mark.parametrize("T", [40, 300])
+def test_gated_workspace_on_an_8_byte_boundary(T):
+    """The workspace needs no alignment of its own: one that starts 8 bytes past a 256-byte
+    boundary, without weight copies, gives the bits of an aligned one."""
+    w = wl.make_ffn("offset workspace", "bf16", T, 512, 1088, seed=T, sparsity=0.95, gated=True, ell_width=128,
+                    tile_slots=64)
+    w.shift_t[::17] = 50.0
+    want = run_forward(w)[0]
+    X, Wu, Wd, Wg = dev(w.X), dev(w.W_up), dev(w.W_down), dev(w.W_gate)
+    cfg = b.make_cfg(**w.cfg)
+    kw = dict(Y=torch.full((T, w.d), float("nan"), dtype=X.dtype, device="cuda"), W_gate=Wg,
+              bufs=b.alloc_twell(T, w.f, "bf16", cfg), shift_t=dev(w.shift_t), stats=b.alloc_stats())
+    n = b.sfl_workspace_size(b.ffn_args(X, Wu, Wd, cfg, **kw))
+    ws = torch.empty(n + 8, dtype=torch.uint8, device="cuda")
+    assert ws.data_ptr() % 256 == 0
+    b.sfl_ffn_forward(b.ffn_args(X, Wu, Wd, cfg, workspace=ws[8:], **kw))
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(host_bits(kw["Y"]), host_bits(want))
+
+
 def test_all_active_and_all_inactive_rows():
     w = wl.make_ffn("extremes", "bf16", 96, 256, 512, seed=3, sparsity=0.95, ell_width=32)
     w.shift_t[:8] = 100.0     # every unit active -> dense-backup rows
