@@ -778,6 +778,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
     g.c_rows = rebuild ? plan.need_slots : nullptr;
     g.C = ovf_dense;
     g.ldc = f;
+    g.tile_m = T;  // fp32: the up projection's sums, so its pre-activations bit for bit
     g.ksplit = kMaxSplit;
     g.part = plan.part;
     g.part_rows = plan.part_rows;

@@ -1667,7 +1667,7 @@ int gemm_split_count(int alay, int blay, const GemmParams& p) {
 hipError_t gemm_f32(int epi, const GemmParams& p, hipStream_t s) {
   if (p.M == 0 || p.N == 0) return hipSuccess;
   // 64 x 64 tiles once they give every CU two blocks, else 32 x 32 (more blocks in flight)
-  const bool big = cdiv(p.M, 64) * cdiv(p.N, 64) >= 2 * device_cus();
+  const bool big = cdiv(p.tile_m ? p.tile_m : p.M, 64) * cdiv(p.N, 64) >= 2 * device_cus();
   switch (epi) {
     case EPI_F32: return big ? launch_f32<EPI_F32, 64>(p, s) : launch_f32<EPI_F32, 32>(p, s);
     case EPI_ACT_RELU: return big ? launch_f32<EPI_ACT_RELU, 64>(p, s) : launch_f32<EPI_ACT_RELU, 32>(p, s);

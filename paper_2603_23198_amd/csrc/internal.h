@@ -78,12 +78,15 @@ struct GemmParams {
   int32_t* tile_sem;
   // order in which output tiles are dealt (TileOrder)
   int tile_order;
+  // fp32 GEMM: the row count that picks the tile, and with it the order of the sums (0: M)
+  int64_t tile_m;
   // EPI_GATED_PAIR: the second B operand (W_up^T beside B = W_gate^T, same shape)
   const void* B2;
   // split-K GEMMs of EPI_ACT_RELU (the few-rows kernel's last blocks, else the reduction
-  // launch), fp32 GEMMs of EPI_ACT_RELU (one atomic per block) and EPI_GATED_PAIR: the sum of the stored |values| is added to
-  // l1_stats->l1_sum (one float64 atomic per tile or per reduction block); the reduction
-  // launch adds the n_l1_more sums at l1_more as well (another kernel's share)
+  // launch), fp32 GEMMs of EPI_ACT_RELU (one atomic per block) and EPI_GATED_PAIR: the sum of
+  // the stored |values| is added to l1_stats->l1_sum (one float64 atomic per tile or per
+  // reduction block); the reduction launch adds the n_l1_more sums at l1_more as well (another
+  // kernel's share)
   sfl_stats_t* l1_stats;
   const float* l1_more;
   int n_l1_more;

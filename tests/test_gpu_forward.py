@@ -462,6 +462,25 @@ def test_fp32_sizes(T, d, f, every):
     assert abs(st["l1_sum"] - H.sum()) <= 1e-5 * max(H.sum(), 1.0)
 
 
+@pytest.mark.parametrize("T,d,f,cap", [(256, 100, 8192, 20), (2100, 130, 1088, 300), (2100, 64, 1088, 0),
+                                       (200, 96, 640, 40)])
+def test_fp32_dense_backup_rows_are_the_up_projections(T, d, f, cap):
+    """fp32 dense-backup rows, recomputed for fewer rows than the batch, are ReLU of the up
+    projection's pre-activations bit for bit (so their active units are the counted ones)."""
+    w = wl.make_ffn("fp32 backup", "f32", T, d, f, seed=T + d, sparsity=0.95, ell_width=f // 8)
+    w.shift_t[::16] += np.float32(0.02 * np.sqrt(d))  # about a quarter of the units: tiles overflow
+    w.cfg["ovf_capacity"] = cap
+    Y, bufs, stats, cfg = run_forward(w)
+    Z = torch.empty((T, f), dtype=torch.float32, device="cuda")
+    b.sfl_up_projection(b.ffn_args(dev(w.X), dev(w.W_up), dev(w.W_down), cfg, shift_t=dev(w.shift_t)), Z)
+    torch.cuda.synchronize()
+    n = int(host_bits(bufs["n_ovf"])[0])
+    assert 0 < n <= (cap or T) and b.read_stats(stats)["capacity_exceeded"] == 0
+    rows = host_bits(bufs["ovf_rows"])[:n]
+    got = host_bits(bufs["ovf_dense"])[:n * f].reshape(n, f)
+    np.testing.assert_array_equal(got, np.maximum(Z.cpu().numpy()[rows], np.float32(0)))
+
+
 @pytest.mark.parametrize("T,d,f,K", [(1, 64, 256, 32), (7, 192, 1024, 64), (64, 704, 512, 48), (200, 960, 1024, 320),
                                      (1030, 192, 1024, 64), (1100, 1600, 2048, 300), (2100, 448, 1088, 96)])
 def test_widths_not_a_multiple_of_512(T, d, f, K):
