@@ -49,10 +49,15 @@ __device__ __forceinline__ void ovf_list_small(int64_t T, const OvfList& ol, con
 }
 
 // Workgroups of tpw tokens (launch_gather_down sizes them); a wave's tokens are wave, wave +
-// 4, .... A token's count, flag and first 64 entries are loaded together (entries past the
-// row's count are read, within the row's K, and not used), so that a row of up to 64 entries
-// waits for memory twice: its entries, then W. ODD: d is odd, the last lane of a row holds
-// one column.
+// 4, .... Small batches (one token per wave) wait on latency: a token's count, flag and first
+// 64 entries are loaded together (entries past the row's count are read, within the row's K,
+// and not used), so that a row of up to 64 entries waits for memory twice: its entries, then
+// W. Large ones are bound by what they read, and there only the row's own entries are loaded.
+// Up to 8 W rows are in flight; they are converted after the last of them is issued, since a
+// conversion beside its load waits for it: bf16, T = 33000, d = 256, f = 4096 at 99 % took
+// 148 us that way, with eight loads for a row's last entries however few and 64 entries read
+// ahead, and 98 us like this (fp32, T = 8192, d = 1024: 102 and 95 us). ODD: d is odd, the
+// last lane of a row holds one column.
 template <typename V, bool ODD>
 __global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K, const V* __restrict__ ell_val,
                                                      const uint16_t* __restrict__ ell_idx,
@@ -76,16 +81,30 @@ __global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K
   const int64_t col = (int64_t)slice * SLICE + 2 * l;
   const bool col_ok = col < d;
   const bool two = !ODD || col + 1 < d;
-  auto load_w = [&](int64_t n) -> float2 {
-    if (!col_ok) return make_float2(0.f, 0.f);
+  // a W_down row's two columns of this lane as they lie in memory (converted after the loads
+  // of a step are all issued)
+  typedef typename std::conditional<sizeof(V) == 2, uint32_t, float2>::type raw_t;
+  auto load_w = [&](int64_t n) -> raw_t {
     if constexpr (sizeof(V) == 2) {
-      const uint32_t w = *(const uint32_t*)(W + n * d + col);
-      return make_float2(bf16lo(w), bf16hi(w));
+      return col_ok ? *(const uint32_t*)(W + n * d + col) : 0u;
+    } else if constexpr (ODD) {
+      float2 w = make_float2(0.f, 0.f);
+      if (col_ok) w.x = W[n * d + col];
+      if (two) w.y = W[n * d + col + 1];
+      return w;
     } else {
-      if (!two) return make_float2(W[n * d + col], 0.f);
-      return *(const float2*)(W + n * d + col);
+      return col_ok ? *(const float2*)(W + n * d + col) : make_float2(0.f, 0.f);
     }
   };
+  auto lo = [](raw_t w) -> float {
+    if constexpr (sizeof(V) == 2) return bf16lo(w);
+    else return w.x;
+  };
+  auto hi = [](raw_t w) -> float {
+    if constexpr (sizeof(V) == 2) return bf16hi(w);
+    else return w.y;
+  };
+  const bool early = tpw == 4 && K > 0;
   for (int tt = wave; tt < tpw; tt += 4) {
     const int64_t t = (int64_t)tb * tpw + tt;
     if (t >= T) break;
@@ -93,22 +112,26 @@ __global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K
     const uint16_t* ei = ell_idx + t * (int64_t)K;
     const uint8_t ovf = row_ovf[t];
     const int cnt_t = row_nnz[t];
-    const int l0 = min(l, max(K - 1, 0));
-    int n_l = K > 0 ? (int)ei[l0] : 0;
-    float v_l = K > 0 ? VT<V>::load(ev, l0) : 0.f;
+    int n_l = 0;
+    float v_l = 0.f;
+    if (early) {
+      const int l0 = min(l, K - 1);
+      n_l = (int)ei[l0];
+      v_l = VT<V>::load(ev, l0);
+    }
     if (__builtin_amdgcn_readfirstlane((int)ovf)) continue;
     const int nnz = __builtin_amdgcn_readfirstlane(cnt_t);
     float a0 = 0.f, a1 = 0.f;
     for (int e0 = 0; e0 < nnz; e0 += 64) {
       const int e = e0 + l;
-      if (e0 > 0) {
+      if (e0 > 0 || !early) {
         n_l = e < nnz ? (int)ei[e] : 0;
         v_l = e < nnz ? VT<V>::load(ev, e) : 0.f;
       }
       const int cnt = min(64, nnz - e0);
       int q = 0;
       for (; q + 8 <= cnt; q += 8) {
-        float2 w[8];
+        raw_t w[8];
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
@@ -117,27 +140,26 @@ __global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          a0 = fmaf(v[u], w[u].x, a0);
-          a1 = fmaf(v[u], w[u].y, a1);
+          a0 = fmaf(v[u], lo(w[u]), a0);
+          a1 = fmaf(v[u], hi(w[u]), a1);
         }
       }
       if (q < cnt) {
-        // the last entries of the row, up to 8: absent ones re-read the last and add nothing
-        float2 w[8];
-        float v[8];
+        // the last entries of the row, up to 7
+        raw_t w[7];
+        float v[7];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int qq = min(q + u, cnt - 1);
-          v[u] = readlane_f(v_l, qq);
-          w[u] = load_w(readlane_i(n_l, qq));
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (q + u < cnt) {
-            a0 = fmaf(v[u], w[u].x, a0);
-            a1 = fmaf(v[u], w[u].y, a1);
+        for (int u = 0; u < 7; ++u)
+          if (q + u < cnt) {  // uniform
+            v[u] = readlane_f(v_l, q + u);
+            w[u] = load_w(readlane_i(n_l, q + u));
           }
-        }
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+          if (q + u < cnt) {
+            a0 = fmaf(v[u], lo(w[u]), a0);
+            a1 = fmaf(v[u], hi(w[u]), a1);
+          }
       }
     }
     if (col_ok) {
