@@ -660,7 +660,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
   OvfList late_list;
   // the slice walk (bf16: over slice-major copies or, at other widths, over W_down itself), or
   // the plain gather in token order
-  const bool slice_walk = bf && (packed_gather(*a) || row_major_walk_ok(d, a->cfg.ell_width));
+  const bool slice_walk = bf && (packed_gather(*a) || row_major_walk(T, d, a->cfg.ell_width));
   const bool token_order = slice_walk && plan.order && nnz_token_order(*a);
   const bool list_by_order = !list_by_gather(*a) && token_order;
   const int n_cls_part = cls_part ? (int)classify_grid(T, f, a->cfg.tile_cols) : 0;
@@ -751,7 +751,7 @@ sfl_status_t forward_run(const sfl_ffn_args_t* a, void* ws, size_t ws_bytes, hip
                                       list_by_order ? OvfList{} : late_list, row_major));
   } else {
     SFL_HIP(launch_gather_down(vb, T, d, a->cfg.ell_width, tw.ell_val, tw.ell_idx, tw.row_nnz, tw.row_ovf, a->W_down,
-                               a->Y, s, late_list));
+                               a->Y, s, late_list, plan.dense_flags ? plan.dense_flags + 1 : nullptr));
   }
   ev.record(3, s);
   // 4. dense-backup rows (Alg. 3, dense part), count on device: the dense ReLU rows are

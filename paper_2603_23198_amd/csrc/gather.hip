@@ -1,7 +1,7 @@
 // Sparse down projections from the compact ELL rows of the hybrid format.
 //
 // Non-gated (Alg. 3, sparse part): y[t, :] = sum_e v[t, e] * W_down[n[t, e], :].
-//  * k_gather_down (fp32, any d; bf16 rows that row_major_walk_ok leaves to it): (d-slice of
+//  * k_gather_down (fp32, any d; bf16 rows that row_major_walk leaves to it): (d-slice of
 //    128 columns) x (block of tokens); a wave owns one token at a time and walks its ELL
 //    entries in order, reading the 128 columns of one W_down row per entry.
 //  * k_gather_down_b16 (bf16): over a slice-major copy of W_down (d % 512 == 0; other widths
@@ -63,8 +63,10 @@ __global__ __launch_bounds__(256) void k_gather_down(int64_t T, int64_t d, int K
                                                      const uint16_t* __restrict__ ell_idx,
                                                      const int32_t* __restrict__ row_nnz,
                                                      const uint8_t* __restrict__ row_ovf, const V* __restrict__ W,
-                                                     V* __restrict__ Y, int n_slices, int n_tb, int tpw, OvfList ol) {
+                                                     V* __restrict__ Y, int n_slices, int n_tb, int tpw, OvfList ol,
+                                                     const int32_t* __restrict__ skip) {
   if (ol.rows && blockIdx.x == 0 && threadIdx.x < 64) ovf_list_small(T, ol, row_ovf);
+  if (skip && *skip) return;  // the dense fallback took this batch
   const int g = blockIdx.x;
   int slice, tb;
   if ((n_slices & 7) == 0) {
@@ -405,6 +407,11 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void k_gather_down_b16(
   int* cnt_s = (int*)(val_s + (size_t)tpw * KV);
   int* tok_s = cnt_s + tpw;
   const int xcd = blockIdx.x & 7;
+  // this XCD's slices of the token block (below)
+  const int full = n_slices >> 3, rem = n_slices & 7;
+  const int extra = RM ? (xcd - (int)(blockIdx.x >> 3) % 8 * rem) & 7 : 0;  // of the slices left over, if < rem
+  const int nsl = RM ? full + (extra < rem ? 1 : 0) : (n_slices - xcd + 7) / 8;
+  if (RM && nsl == 0) return;  // fewer than 8 slices: none of this block's
   const int64_t t0 = (int64_t)(blockIdx.x >> 3) * tpw;
   const int l = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -511,9 +518,6 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void k_gather_down_b16(
   // work items (slice of this XCD, token) in slice-major order, dealt round-robin to the
   // waves: the workgroup walks the slices in order, and a small block (decode) still
   // keeps every wave busy
-  const int full = n_slices >> 3, rem = n_slices & 7;
-  const int extra = RM ? (xcd - (int)(blockIdx.x >> 3) % 8 * rem) & 7 : 0;  // of the slices left over, if < rem
-  const int nsl = RM ? full + (extra < rem ? 1 : 0) : (n_slices - xcd + 7) / 8;
   auto slice_of = [&](int k) -> int { return RM && k == full ? 8 * full + extra : xcd + 8 * k; };
   auto slice_byte = [&](int slice) -> uint32_t {
     return RM ? (uint32_t)slice * (SLICE2 * 2) : (uint32_t)(slice * f * SLICE2 * 2);
@@ -1123,7 +1127,7 @@ static int slice_walk_tpw(int64_t T, int64_t per_tok);
 // 4 tokens (32 workgroups) 3.5 us.
 hipError_t launch_gather_down(int val_bf16, int64_t T, int64_t d, int K, const void* ell_val, const uint16_t* ell_idx,
                               const int32_t* row_nnz, const uint8_t* row_ovf, const void* W, void* Y, hipStream_t s,
-                              OvfList ol) {
+                              OvfList ol, const int32_t* skip) {
   if (val_bf16 && d % 2 != 0) return hipErrorInvalidValue;
   if (T == 0) return hipSuccess;
   if (ol.rows && (T > 64 || !ol.n)) return hipErrorInvalidValue;
@@ -1134,7 +1138,7 @@ hipError_t launch_gather_down(int val_bf16, int64_t T, int64_t d, int K, const v
   const dim3 grid((unsigned)(n_slices * n_tb));
 #define SFL_GATHER_DOWN(V_, ODD_)                                                                              \
   hipLaunchKernelGGL((k_gather_down<V_, ODD_>), grid, dim3(256), 0, s, T, d, K, (const V_*)ell_val, ell_idx, row_nnz, \
-                     row_ovf, (const V_*)W, (V_*)Y, n_slices, n_tb, tpw, ol)
+                     row_ovf, (const V_*)W, (V_*)Y, n_slices, n_tb, tpw, ol, skip)
   if (val_bf16) SFL_GATHER_DOWN(bf16_t, false);
   else if (d % 2 == 0) SFL_GATHER_DOWN(float, false);
   else SFL_GATHER_DOWN(float, true);
@@ -1146,6 +1150,21 @@ hipError_t launch_gather_down(int val_bf16, int64_t T, int64_t d, int K, const v
 // each) in a workgroup's LDS, 160 KB, with room to spare, and the byte stride of a W_down row
 // in the 24 bits of slice_token's multiply.
 bool row_major_walk_ok(int64_t d, int K) { return K <= 32768 && d < (int64_t)1 << 23; }
+
+// The walk stages a token's entries once per XCD that has a slice of it, however few they are;
+// the plain gather reads them once per 128 columns. Where rows are short (K bounds them) and
+// narrow, large batches are faster in the plain gather; the bound counts its 128-column slices
+// (one that is half used as one and a half), rows of fewer than 64 entries as 64. Classification
+// to end of gather, plain / walk in us: K = 64 (10 active units of f = 1024), T = 16384: d = 128
+// 43 / 66, 256 52 / 66, 448 60 / 66, 576 68 / 68, 960 85 / 71; K = 128 (41 of 4096), T = 33000:
+// d = 128 122 / 169, 192 152 / 131, 256 152 / 169, 576 240 / 186; K = 192 (82 of 8192),
+// T = 33000: d = 128 163 / 199, 256 219 / 198. Up to about 10000 tokens the two differ by less
+// than the rest of the call varies (T = 8192, K = 64: d = 256 36 / 43, 448 46 / 44).
+bool row_major_walk(int64_t T, int64_t d, int K) {
+  const int64_t half_slices = 2 * cdiv(d, SLICE) + (d % SLICE != 0 ? 1 : 0);
+  const bool short_rows = half_slices * std::max(K, 64) <= 576;
+  return row_major_walk_ok(d, K) && !(T >= 10240 && short_rows);
+}
 
 hipError_t launch_gather_down_packed(int64_t T, int64_t d, int64_t f, int K, const void* ell_val,
                                      const uint16_t* ell_idx, const int32_t* row_nnz, const uint8_t* row_ovf,

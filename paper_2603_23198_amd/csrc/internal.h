@@ -212,10 +212,11 @@ struct OvfList {
   sfl_stats_t* stats = nullptr;
 };
 // Y[t, :] = sum_e ell_val[t][e] * W[ell_idx[t][e], :] for rows with row_ovf[t] == 0. With
-// ol.rows (at most 64 rows): block 0 also builds the dense-backup row list from row_ovf.
+// ol.rows (at most 64 rows): block 0 also builds the dense-backup row list from row_ovf. With
+// skip, nothing else is done where *skip is set.
 hipError_t launch_gather_down(int val_bf16, int64_t T, int64_t d, int ell_width, const void* ell_val,
                               const uint16_t* ell_idx, const int32_t* row_nnz, const uint8_t* row_ovf, const void* W,
-                              void* Y, hipStream_t s, OvfList ol = OvfList());
+                              void* Y, hipStream_t s, OvfList ol = OvfList(), const int32_t* skip = nullptr);
 // order[0 .. T): the sparse rows by descending row_nnz, then the dense-backup rows (one
 // workgroup, counting sort over K + 2 buckets; order within a bucket unspecified; with
 // row_ovf null every row counts as sparse and counts above K share the first bucket).
@@ -230,6 +231,8 @@ hipError_t launch_nnz_order(int64_t T, int K, const int32_t* row_nnz, const uint
 // bf16, d % 512 == 0: same sum from the slice-major copy of W_down (XCD-aware); row_major
 // (d % 64 == 0; bf16 values, out_mode 0; row_major_walk_ok): from W_down [f][d] itself.
 bool row_major_walk_ok(int64_t d, int ell_width);
+// Whether a forward of T tokens takes it (else launch_gather_down).
+bool row_major_walk(int64_t T, int64_t d, int ell_width);
 // out_mode 0: bf16 Y; 1: fp32 Yf; 2: bf16 Y of (sum + Yf) (val_f32 only for 1 and 2).
 // With ol.rows (at most 64 rows): block 0 also builds the dense-backup row list from row_ovf
 // (as launch_ovf_list would), before anything else.

@@ -499,6 +499,25 @@ def test_widths_not_a_multiple_of_512(T, d, f, K):
         assert np.linalg.norm(Yg[t] - Yref[t]) <= 2e-2 * np.linalg.norm(Yref[t]), t
 
 
+@pytest.mark.parametrize("T,d,f,K", [(10239, 64, 256, 8), (10240, 64, 256, 8), (10250, 448, 320, 64),
+                                     (10250, 576, 320, 64), (10301, 128, 640, 192), (10301, 192, 640, 128)])
+@pytest.mark.parametrize("sparsity", [0.995, 0.6])
+def test_short_rows_of_large_batches(T, d, f, K, sparsity):
+    """Large batches at narrow widths, on both sides of the sizes at which the plain gather
+    serves short rows instead of the walk, with dense-backup and empty rows; at 60 % with the
+    dense fallback deciding (K >= f / 32): every row of Y against the oracle."""
+    w = wl.make_ffn("short rows", "bf16", T, d, f, seed=d + K, sparsity=sparsity, ell_width=K, tile_slots=128)
+    w.shift_t[::1001] = 50.0
+    w.shift_t[3::1001] = -1e4
+    Y, bufs, _, cfg = run_forward(w)
+    Yref, _ = oracle_rows(w, np.arange(T))
+    Yg = to_f64(Y)
+    assert rel_l2(Yg, Yref) <= 2e-2
+    assert (Yg[3::1001] == 0).all()
+    bad = np.linalg.norm(Yg - Yref, axis=1) > 3e-2 * np.linalg.norm(Yref, axis=1)
+    assert not bad.any(), np.nonzero(bad)[0][:10]
+
+
 def test_row_stride_past_24_bits():
     """A width whose W_down rows are 2^24 bytes apart or more (so f = 64): the sampled columns
     of every row against the float64 product over the active units, half of them."""
