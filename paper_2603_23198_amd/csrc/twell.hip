@@ -615,11 +615,16 @@ hipError_t launch_pack_classify_rows(const float* Z, int ks, const float* bias, 
 // the quarter's entries so far, its place among the quarter's entries. These wait in LDS for
 // the row's total and the counts of the quarters before, and then go to the slabs and (unless
 // the row is a dense-backup one) to the ELL row 64 per store: stored as they are found, each
-// register of four columns took its own nearly empty store instructions. A quarter of more
-// than K entries, necessarily of a dense-backup row, is walked again to store its slabs. Two
-// blocks per CU (at most 64 VGPRs and 96 SGPRs). T = 4001, f = 5600 (90 MB of Z): the entry
-// point 57.0 us with one wave per (row, tile) and a classification of its own, 41.6 with the
-// entries stored as found, 35.0 now.
+// register of four columns took its own nearly empty store instructions. From the group of
+// steps on in which a quarter has more than K entries, or after the one in which a tile has
+// more than S, its row is a dense-backup one and entries go to the slabs as they are found
+// (T = 3000, f = 16384 with half the columns active: 70 us; 87 with such quarters walked a
+// second time from their start). Two blocks per CU (at most 64 VGPRs and 96 SGPRs). T = 4001,
+// f = 5600 (90 MB of Z): the entry point 57.0 us with one wave per (row, tile) and a
+// classification of its own, 41.6 with the entries stored as found, 35.0 now. Batches in which
+// every row is a dense-backup one, of quarters of one group, gain nothing over the two launches
+// (f = 5632, half active: T = 300 19.6 against 18.9 us, T = 1000 23.9 against 19.3, T = 6000
+// 66 against 64): each such quarter is read twice.
 constexpr int kPackRowsWaves = 16;                   // per block
 constexpr int kPackRowsParts = 4;                    // waves per row
 constexpr int kPackRowsUnroll = 6;
@@ -664,14 +669,18 @@ __global__ __launch_bounds__(kPackRowsWaves * 64, 8) void k_pack_rows(
         idx[at] = (uint16_t)col;
       }
     };
-    // the quarter's columns: its entries into LDS (as many as fit) and its tiles' counts to
-    // memory, or, with DIRECT, its entries to the slabs
-    auto walk = [&](auto direct) {
+    // the quarter's columns from c0 on: its tiles' counts to memory and its entries into LDS,
+    // or, with DIRECT, to the slabs. Without, it ends early where the row is seen to be a
+    // dense-backup one, which it looks at after each group of steps (a look after every step
+    // cost sparse rows 3 %): after the group if a tile overflowed, before it if its entries do
+    // not fit. Returns the column reached.
+    auto walk = [&](auto direct, int c0) -> int {
       constexpr bool DIRECT = decltype(direct)::value;
       const float* zr = Z + t * f;
-      mine = 0;
-      over = 0;
-      for (int c0 = c_lo; c0 < c_hi; c0 += 256 * kPackRowsUnroll) {
+      int mine0 = 0, over0 = 0;
+      for (; c0 < c_hi && (DIRECT || (over == 0 && mine <= K)); c0 += 256 * kPackRowsUnroll) {  // uniform
+        mine0 = mine;
+        over0 = over;
         float4 z[kPackRowsUnroll];  // columns past the row re-read its last four and are not active
 #pragma unroll
         for (int u = 0; u < kPackRowsUnroll; ++u) z[u] = *(const float4*)(zr + (uint32_t)min(c0 + u * 256 + 4 * l, f - 4));
@@ -717,17 +726,23 @@ __global__ __launch_bounds__(kPackRowsWaves * 64, 8) void k_pack_rows(
             pos += act ? 1 : 0;
           }
           const bool first = in && l == gsh;
-          if (!DIRECT && first) {
+          if (first) {
             if constexpr (PK) ((uint32_t*)val)[t * row_words + j * 32] = (uint32_t)cnt_tile;
             else cnt[t * NT + j] = cnt_tile;
           }
           over += __popcll(ballot(first && cnt_tile > S));
         }
       }
+      if (DIRECT || mine <= K) return c0;
+      mine = mine0;
+      over = over0;
+      return c0 - 256 * kPackRowsUnroll;
     };
+    int staged = 0;
     if (t < T) {
-      walk(std::false_type{});
-      if (mine > K) walk(std::true_type{});  // uniform
+      const int c = walk(std::false_type{}, c_lo);
+      staged = mine;
+      if (c < c_hi) walk(std::true_type{}, c);  // uniform
     }
     if (l == 0) {
       w_cnt[turn][w] = mine;
@@ -754,18 +769,16 @@ __global__ __launch_bounds__(kPackRowsWaves * 64, 8) void k_pack_rows(
       nnz_sum += total;
       over_sum += over;
     }
-    if (mine <= K) {
-      const bool ell = !ovf && keep;
-      for (int e = l; e < mine; e += 64) {
-        const V v = ev[e];
-        const uint16_t c = ec[e];
-        const int slot = es[e];
-        if (slot < S) store_slot(c, slot, v);
-        if (ell && l1_vals) l1 += VT<V>::load(&v, 0);
-        if (ell && ell_val) {
-          ell_val[t * (int64_t)K + before + e] = v;
-          ell_idx[t * (int64_t)K + before + e] = c;
-        }
+    const bool ell = !ovf && keep;  // then all of the quarter's entries are in LDS
+    for (int e = l; e < staged; e += 64) {
+      const V v = ev[e];
+      const uint16_t c = ec[e];
+      const int slot = es[e];
+      if (slot < S) store_slot(c, slot, v);
+      if (ell && l1_vals) l1 += VT<V>::load(&v, 0);
+      if (ell && ell_val) {
+        ell_val[t * (int64_t)K + before + e] = v;
+        ell_idx[t * (int64_t)K + before + e] = c;
       }
     }
     __builtin_amdgcn_wave_barrier();  // all lanes are done with the quarter's entries

@@ -5,11 +5,12 @@ import pytest
 import torch
 
 from oracle import twell
-from tests.gpu_util import assert_twell_equal, dev, twell_views
+from tests.gpu_util import assert_twell_equal, dev, host_bits, twell_views
 
 pytestmark = pytest.mark.gpu
 
 b = pytest.importorskip("paper_2603_23198_amd.binding")
+from tests.test_gpu_packed32 import assert_words_equal, got_words  # noqa: E402
 
 
 def special_z(T, f, seed, density=0.05):
@@ -81,6 +82,54 @@ def test_pack_bit_exact(T, f, Tn, S, K, cap, dt):
     assert st["n_ovf_rows"] == n_ovf
     assert st["n_tile_ovf"] == hy.n_tile_ovf
     assert st["capacity_exceeded"] == int(n_ovf > capv)
+
+
+@pytest.mark.parametrize("Tn,S,K,dt,packed", [(256, 32, 100, "bf16", False), (256, 256, 130, "bf16", False),
+                                              (128, 128, 100, "f32", False), (64, 8, 722, "f32", False),
+                                              (256, 31, 100, "bf16", True), (128, 31, 130, "bf16", True),
+                                              (64, 31, 1011, "bf16", True)])
+def test_rows_turn_dense_anywhere(Tn, S, K, dt, packed):
+    """Four waves per row, three groups of steps per wave (f = 13000): rows that exceed the ELL
+    width or a tile's slots in the first, a middle or the last step of a quarter, in one quarter
+    only, throughout or not at all: the slabs (planes or packed words), counts, flags, ELL rows
+    and statistics are the oracle's bit for bit."""
+    T, f, quarter = 301, 13000, 3328
+    r = np.random.default_rng(Tn + S + K)
+    Z = -np.abs(r.standard_normal((T, f)).astype(np.float32)) - np.float32(0.1)
+    on = np.zeros((T, f), dtype=bool)
+    on[0::10] = r.random((len(on[0::10]), f)) < 0.0005
+    on[1::10] = r.random((len(on[1::10]), f)) < 0.7 * K / f
+    on[2::10] = True
+    for q in range(4):
+        on[4::10, q * quarter + 3072:(q + 1) * quarter] = True   # the last step of every quarter
+        on[5::10, q * quarter + 1700:q * quarter + 1900] = True  # in the second group
+        on[6::10, q * quarter:q * quarter + 9] = True            # one tile, in the first step
+    on[7::10] = r.random((len(on[7::10]), f)) < 0.1
+    on[8::10, quarter:2 * quarter] = True                        # one quarter only
+    on[9::10, -1::-20] = True
+    Z[on] *= -1
+    layout = b.SFL_TWELL_PACKED32 if packed else 0
+    cfg = b.make_cfg(tile_cols=Tn, tile_slots=S, ell_width=K, layout=layout)
+    bufs, stats = b.alloc_twell(T, f, dt, cfg), b.alloc_stats()
+    b.sfl_pack_twell(dev(Z), dt, cfg, bufs, stats)
+    torch.cuda.synchronize()
+    tw = twell.extract_twell(Z, Tn, S, dt)
+    hy = twell.classify(tw, K)
+    if packed:
+        assert_words_equal(got_words(bufs, T, f, Tn), twell.pack32(tw))
+        for name in ("row_nnz", "row_ovf"):
+            np.testing.assert_array_equal(host_bits(bufs[name])[:T], {"row_nnz": hy.row_nnz, "row_ovf": hy.is_ovf}[name])
+        for name in ("ell_idx", "ell_val"):
+            got, want = host_bits(bufs[name])[:T * K].reshape(T, K), getattr(hy, name)
+            used = (np.arange(K) < hy.row_nnz[:, None]) & ~hy.is_ovf[:, None]
+            np.testing.assert_array_equal(got[used], want[:, :K][used])
+    else:
+        assert_twell_equal(twell_views(bufs, T, f, cfg), tw, hy)
+    st = b.read_stats(stats)
+    assert 0 < len(hy.ovf_rows) < T and st["n_ovf_rows"] == len(hy.ovf_rows)
+    assert st["total_nnz"] == int(tw.cnt.sum()) and st["n_tile_ovf"] == hy.n_tile_ovf
+    kept = twell.stored_to_f64(hy.ell_val, dt).sum()
+    assert abs(st["l1_sum"] - kept) <= 1e-5 * kept
 
 
 def test_pack_is_deterministic():
