@@ -788,9 +788,10 @@ __global__ __launch_bounds__(kPackRowsWaves * 64, 8) void k_pack_rows(
 
 // Rows of whole 16-byte chunks, tiles of 64, 128 or 256 columns, and ELL entries that fit the
 // waves' LDS; batches of more than kRowPackMaxRows rows (the one-workgroup-per-row kernel
-// spreads smaller ones over more of the GPU), and rows in which each of the four waves has
-// columns: T = 8000, f = 100 took 27.1 us against 25.6 with pack and classification apart
-// (f = 5600: 35.0 against 57.0 us, T = 300, f = 16384: 20.4 against 21.0).
+// spreads smaller ones over more of the GPU), and rows of at least four 256-column steps (in
+// some lengths the fourth wave has none all the same: a quarter is whole steps). T = 8000, f =
+// 100 took 27.1 us against 25.6 with pack and classification apart (f = 5600: 35.0 against
+// 57.0 us, T = 300, f = 16384: 20.4 against 21.0).
 bool pack_rows_ok(int64_t T, int64_t f, int Tn, int K, int val_bf16) {
   if (T <= kRowPackMaxRows || f % 4 != 0 || f <= 256 * (kPackRowsParts - 1) || f > 65535) return false;
   if (Tn != 64 && Tn != 128 && Tn != 256) return false;
@@ -804,8 +805,13 @@ hipError_t launch_pack_rows(const float* Z, int64_t T, int64_t f, int val_bf16, 
   if (packed && (!val_bf16 || S != 31)) return hipErrorInvalidValue;
   const int NT = (int)cdiv(f, Tn);
   const size_t lds = (size_t)kPackRowsWaves * K * (3 + (val_bf16 ? 2 : 4));
-  // at most 512 blocks (two per CU): their statistics are added by same-address atomics
-  const dim3 grid((unsigned)std::min<int64_t>(cdiv(T, kPackRowsPerBlock), 512)), block(kPackRowsWaves * 64);
+  // Two blocks per CU, or one where the batch is small: the blocks of a short launch end
+  // together and add their statistics (if asked for) to the same addresses, about 10 ns each (entry point at
+  // 99 %, 512 / 256 blocks: T = 2048, f = 1028 22.5 / 18.6 us, f = 4096 24.1 / 21.4; T = 3500,
+  // f = 4096 32.3 / 27.2; T = 6000, f = 2304 31.0 / 32.6; T = 4096, f = 5632 33.5 / 35.8; with
+  // every row a dense-backup one T = 3000, f = 5632 44 / 45).
+  const int64_t blocks = stats && T <= 4096 && T * f <= 14000000 ? 256 : 512;
+  const dim3 grid((unsigned)std::min(cdiv(T, kPackRowsPerBlock), blocks)), block(kPackRowsWaves * 64);
 #define SFL_PACK_ROWS_TN(V_, PK_, TN_)                                                                            \
   if (lds > 65536) {                                                                                              \
     const hipError_t e = hipFuncSetAttribute((const void*)k_pack_rows<V_, PK_, TN_>,                              \

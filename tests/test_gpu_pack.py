@@ -43,18 +43,21 @@ CASES = [
     (3, 1984, 256, 32, 64, 0, "bf16"),       # partial last tile
     (17, 320, 128, 128, 500, 0, "f32"),      # every column of a tile kept
     (2, 24576, 256, 32, 400, 0, "bf16"),     # a row of 96 KB of fp32 in LDS
-    # above 256 rows with f a multiple of 4: four waves per row pack and classify
+    # above 256 rows with f at most 768: pack and classification apart
     (257, 4, 64, 4, 2, 0, "bf16"),
     (300, 260, 256, 16, 14, 0, "bf16"),      # partial last tile
+    (8300, 132, 64, 12, 12, 0, "f32"),
+    (300, 768, 256, 16, 40, 0, "bf16"),
+    # f above that and a multiple of 4: four waves per row pack and classify
     (700, 1284, 128, 16, 60, 9, "f32"),      # partial last step, capacity below the overflow rows
     (513, 1024, 64, 8, 0, 0, "bf16"),        # every active row is a dense-backup row
-    (8300, 132, 64, 12, 12, 0, "f32"),       # more rows than waves
-    (300, 768, 256, 16, 40, 0, "bf16"),      # pack and classification apart
     (300, 772, 256, 16, 40, 0, "bf16"),      # the fourth wave with one lane of columns
     (300, 8192, 256, 32, 1011, 0, "bf16"),   # the widest ELL rows the waves' LDS holds
     (300, 8192, 256, 32, 1012, 0, "bf16"),   # wider: pack and classification apart
     (300, 8192, 128, 32, 722, 0, "f32"),     # the widest in float32
     (301, 4096, 256, 256, 40, 0, "bf16"),    # quarters of a row on both sides of K entries
+    (1501, 1284, 256, 24, 80, 0, "bf16"),    # more rows than 256 blocks take at once
+    (4097, 772, 64, 16, 50, 0, "f32"),       # than 512 blocks, the last block with one row
 ]
 
 
