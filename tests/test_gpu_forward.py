@@ -182,24 +182,46 @@ def test_fused_twell_equals_pack_of_same_mainloop(T, f, Tn, S, use_wupt):
     assert rel_l2(to_f64(Y)[rows], Yref) <= 2e-2
 
 
+def expected_tile(T, f):
+    """(rows, rounds) of the TwELL GEMM's output tile: the height whose rounds of one tile per CU
+    cost least, 128-row tiles at 0.62 and 64-row ones at 0.47 of a round of 256-row tiles, a
+    smaller tile for a gain of 15 % or more; rounds are the most tiles that one block takes."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rounds = {r: -(-(-(-T // r) * -(-f // 256)) // cus) for r in (256, 128, 64)}
+    best, least = 256, rounds[256] * 100
+    for rows, cost in ((128, 62), (64, 47)):
+        if rounds[rows] * cost * 115 < least * 100:
+            best, least = rows, rounds[rows] * cost
+    return best, rounds[best]
+
+
 @pytest.mark.parametrize("use_wupt", [False, True])
-@pytest.mark.parametrize("T,d,f,Tn,S,layout", [
-    (257, 64, 320, 256, 32, 0), (321, 128, 1984, 256, 31, 1), (259, 192, 1088, 64, 16, 0),   # 64-row tiles
-    (530, 64, 14336, 128, 16, 0), (530, 256, 14336, 256, 32, 0),                            # 64 rows, two rounds
-    (300, 64, 16384, 256, 32, 0), (1000, 192, 5632, 128, 16, 0), (900, 128, 5632, 256, 31, 1),  # 128 rows
-    (3000, 192, 5632, 64, 8, 0)])                                                           # 128 rows, three rounds
-def test_fused_twell_tile_heights(T, d, f, Tn, S, layout, use_wupt):
-    """The TwELL GEMM picks 64-, 128- or 256-row tiles by the number of tiles: at every height
-    (one to four K steps around the ring of stages, ragged T and f, one and several tiles per
-    block, both weight layouts, planes and packed words) the TwELL is the oracle's extraction
-    of the same main loop's float32 pre-activations, bit for bit."""
+@pytest.mark.parametrize("T,d,f,Tn,S,layout,tile", [
+    (257, 64, 320, 256, 32, 0, (64, 1)), (321, 128, 1984, 256, 31, 1, (64, 1)),
+    (259, 192, 1088, 64, 16, 0, (64, 1)), (509, 256, 5632, 128, 16, 0, (64, 1)),
+    (300, 64, 16384, 256, 32, 0, (128, 1)), (1000, 192, 5632, 128, 16, 0, (128, 1)),
+    (900, 128, 5632, 256, 31, 1, (128, 1)),
+    # several 128-row tiles per block: the next tile's stages, bias and shift loading beside the
+    # epilogue of the one before, at one to four K steps around the ring of three stages
+    (1100, 64, 14336, 256, 32, 0, (128, 2)), (1100, 192, 14336, 256, 31, 1, (128, 2)),
+    (1100, 256, 14336, 64, 8, 0, (128, 2)), (2175, 64, 15360, 64, 8, 0, (128, 4)),
+    (2175, 128, 15360, 128, 16, 0, (128, 4)), (2175, 256, 15360, 256, 31, 1, (128, 4)),
+    (530, 64, 14336, 128, 16, 0, (256, 1)), (3000, 192, 5632, 64, 8, 0, (256, 2))])
+def test_fused_twell_tile_heights(T, d, f, Tn, S, layout, tile, use_wupt):
+    """The TwELL GEMM picks 64-, 128- or 256-row tiles by the number of tiles: at every height,
+    and with several tiles per block of 128 and 256 rows (64-row tiles fill at most one round
+    wherever they are taken), for one to four K steps, ragged T and f, a bias per column, both
+    weight layouts, planes and packed words, the TwELL is the oracle's extraction of the same
+    main loop's float32 pre-activations, bit for bit."""
+    assert expected_tile(T, f) == tile
     w = wl.make_ffn("tile heights", "bf16", T, d, f, seed=T + d, sparsity=0.98, tile_cols=Tn, tile_slots=S,
                     ell_width=512)
+    w.bias_f = (np.random.default_rng(T + d).standard_normal(f) * 0.02).astype(np.float32)
     w.cfg["layout"] = layout
     _, bufs, _, cfg = run_forward(w, use_wupt=use_wupt)
     X, Wu = dev(w.X), dev(w.W_up)
     Z = torch.empty((T, f), dtype=torch.float32, device="cuda")
-    b.sfl_up_projection(b.ffn_args(X, Wu, dev(w.W_down), cfg, shift_t=dev(w.shift_t),
+    b.sfl_up_projection(b.ffn_args(X, Wu, dev(w.W_down), cfg, shift_t=dev(w.shift_t), bias_f=dev(w.bias_f),
                                    W_upT=transposed(Wu) if use_wupt else None), Z)
     torch.cuda.synchronize()
     tw = twell.extract_twell(Z.cpu().numpy(), Tn, S, "bf16")
