@@ -28,7 +28,7 @@
  *    one GPU (they share its scratch array).
  *  - Environment: the persistent GEMMs (the up or gate projection of
  *    sfl_ffn_forward and sfl_up_projection, the GEMMs of sfl_dense_ffn_baseline and
- *    of the dense fallback) deal their 256 x 256 output tiles along a Hilbert curve
+ *    of the dense fallback) deal their output tiles along a Hilbert curve
  *    over square blocks of tiles (the paper's persistent-GEMM schedule) where the
  *    tile grid is made of such squares, and in an XCD-grouped order otherwise;
  *    SFL_GEMM_TILE_ORDER=grouped selects the grouped order everywhere. Results are

@@ -6,9 +6,9 @@
 //    entries in order, reading the 128 columns of one W_down row per entry.
 //  * k_gather_down_b16 (bf16): over a slice-major copy of W_down (d % 512 == 0; other widths
 //    over W_down itself), each XCD walking its own 64-column slices so that one 2 MiB slice
-//    stays in its L2 while every token streams through it (see below). A work item is (slice, token), the 8 lane
-//    groups of the wave splitting the token's entries and folding their sums, or, for
-//    large batches of short rows, (slice, 8 tokens), one token per lane group.
+//    stays in its L2 while every token streams through it (see below). A work item is (slice,
+//    token), the 8 lane groups of the wave splitting the token's entries and folding their
+//    sums, or, for large batches of short rows, (slice, 8 tokens), one token per lane group.
 //
 // Gated (Alg. 2 / eq. sec3:eq:twell_to_dense_fused_matmul): per active gate value g at
 // column n, u = x[t] . W_up[:, n] and y[t] += (g * u) W_down[n]. Done in two passes with
@@ -1090,8 +1090,8 @@ __global__ __launch_bounds__(256) void k_pack_down(const bf16_t* __restrict__ W,
 
 // Slice-major copy of W^T straight from W [d][f]: out[s][n][c] = W[64 s + c][n]. A block moves
 // one 64 x 64 tile through LDS, whose output is 8 KB in one piece: W is read once and written
-// once, where a transpose followed by k_pack_down moved it twice (d = 4096, f = 14336: 103 +
-// 39 us; this 45). Reads are 16 bytes of a W row per lane, writes 16 bytes (8 c) of one n. LDS
+// once, where a transpose followed by k_pack_down moved it twice (d = 4096, f = 14336: 118 +
+// 38 us; this 41). Reads are 16 bytes of a W row per lane, writes 16 bytes (8 c) of one n. LDS
 // rows of 66 values keep both sides' 2- and 4-byte accesses at two lanes per bank.
 __global__ __launch_bounds__(256) void k_pack_transposed(const bf16_t* __restrict__ W, bf16_t* __restrict__ out,
                                                          int64_t f) {

@@ -1,20 +1,21 @@
 // Dense GEMMs of the FFN layer: bf16 and fp32, on MFMA.
 //
-// Two bf16 kernels, both 256x256 output tiles per workgroup of 8 waves:
-//  * k_gemm_kc (both operands K-contiguous, K % 64 == 0; the forward's X W_up^T, the
-//    dense baseline's first GEMM, the backward's dZ W_up^T): v_mfma_f32_16x16x32_bf16,
-//    waves 4 along M x 2 along N, operands loaded straight from global memory into LDS
-//    (no staging registers) through two 64-k stages; persistent blocks, one per CU. Its
-//    split-K forms (k_gemm_kc_split, and k_gemm_few_rows for at most 64 rows) serve
-//    small batches and the dense-backup rows.
+// Two bf16 kernels, workgroups of 8 waves:
+//  * k_gemm_kc (A K-contiguous, B K- or row-contiguous, K % 64 == 0; the forward's X W_up, the
+//    dense baseline's GEMMs, the backward's dZ W_up^T): v_mfma_f32_16x16x32_bf16, 256 x 256
+//    output tiles (with the TwELL epilogue also 128 x 256 and 64 x 256), operands loaded
+//    straight from global memory into LDS (no staging registers) through a ring of two 64-k
+//    stages (three for the smaller tiles); persistent blocks, one per CU. Its split-K forms
+//    (k_gemm_kc_split, and k_gemm_few_rows for at most 64 rows) serve small batches and the
+//    dense-backup rows.
 //  * k_gemm_bf16 (any layout pair, K gathers, device-side K bounds): v_mfma_f32_32x32x16,
-//    waves 2 along M x 4 along N (128x64 per wave = 4x2 MFMA 32x32 tiles). K advances in
-//    steps of 64 through a double-buffered LDS stage; the next K step is fetched from
-//    global memory into registers while the current one feeds the MFMAs. Each operand
+//    256 x 256 tiles, waves 2 along M x 4 along N (128x64 per wave = 4x2 MFMA 32x32 tiles). K
+//    advances in steps of 64 through a double-buffered LDS stage; the next K step is fetched
+//    from global memory into registers while the current one feeds the MFMAs. Each operand
 //    tile is kept in LDS K-contiguous ([rows][64 + 8 pad] bf16). Operands stored
-//    row-contiguous ([K][rows], e.g. W_up [d][f] as the B of X W_up) are transposed on
-//    the way in: a lane fetches one 4-byte pair of adjacent rows from 8 consecutive k,
-//    and byte permutes turn them into two 8-element k vectors.
+//    row-contiguous ([K][rows], e.g. W_up [d][f] as the B of X W_up) are transposed on the way
+//    in: a lane fetches one 4-byte pair of adjacent rows from 8 consecutive k, and byte
+//    permutes turn them into two 8-element k vectors.
 //
 // Epilogues (the `Epilogue` enum) include the TwELL one of Alg. 1, which compacts the
 // active pre-activations straight from the accumulator registers (a ballot per register
@@ -771,9 +772,10 @@ struct KcOps {
   // be read and the buffer of stage kt-1 refilled with stage kt+NS-1. SPREAD deals the
   // refill's loads over the first half step's MFMAs, B's (the weights, which come from
   // further away) before A's, instead of issuing them in one burst that the fragment reads
-  // then queue behind: the up GEMM with the TwELL epilogue at T = 8192, d = 4096, f = 16384
-  // 0.855 -> 0.844 ms with warm weights, at 64-row tiles (T = 509, d = 2048, f = 5632) 28 ->
-  // 26 us; the dense down GEMM (K = 16384) went 0.800 -> 0.832 ms and keeps the burst.
+  // then queue behind: the up GEMM with the TwELL epilogue at T = 1024, d = 4096, f = 16384
+  // 116 -> 112 us, at 64-row tiles (T = 509, d = 2048, f = 5632) 30.1 -> 29.4 us (kernel
+  // traces, warm weights); the dense down GEMM (K = 16384) went 0.800 -> 0.832 ms and keeps
+  // the burst.
   template <bool SPREAD>
   __device__ __forceinline__ void run(const GemmParams& p, bf16_t* smem, int b0, int kt_begin, int kt_end,
                                       typename W::Acc& acc) const {
@@ -1291,11 +1293,11 @@ int device_cus() {
 // least, a round of 128-row tiles at 0.62 and of 64-row tiles at 0.47 of a round of 256-row
 // ones (measured at K = 1024, 2048 and 4096 with idle CUs left). A 256-row tile does the most
 // work per byte loaded and wins wherever its tiles fill the CUs; up to about a thousand rows
-// they do not: T = 509, d = 2048, f = 5632 (44, 88 or 176 tiles) 57, 35 and 26 us, T = 300,
-// d = 4096, f = 16384 (128, 192 or 320) 99, 61 and 90 us, T = 1024 (256, 512 or 1024) 115, 141
-// and 200 us. Smaller tiles have to promise a gain of 15 %: a last round that is mostly empty
-// costs the 256-row tiles less than a full one (T = 1500, f = 16384: 2 rounds against 3 of
-// 128-row tiles, 218 and 214 us).
+// they do not (kernel traces): T = 509, d = 2048, f = 5632 (44, 88 or 176 tiles) 54, 37 and 29
+// us, T = 300, d = 4096, f = 16384 (128, 192 or 320) 96, 62 and 90 us, T = 1024 (256, 512 or
+// 1024) 112, 133 and 182 us. Smaller tiles have to promise a gain of 15 %, since a last round
+// that is mostly empty costs the 256-row tiles less than a full one: T = 1500, f = 16384, 2
+// rounds against 3 of 128-row tiles, 204 and 193 us.
 int kc_tile_rows(const GemmParams& p) {
   constexpr int rows[] = {256, 128, 64}, cost[] = {100, 62, 47};
   int best = BM;
@@ -1409,7 +1411,7 @@ hipError_t launch_twell(const GemmParams& p, hipStream_t s) {
 // layer's fp32 batches are small and latency bound, so a step is as deep as the registers
 // allow (at BT = 32, d = 256 takes two), and 32 x 32 tiles are used where 64 x 64 ones leave
 // CUs idle: at T = 64, d = 256, f = 1024 the up GEMM takes
-// 6.3 us with 64 tiles of 32 x 32 (16-k steps on 16 tiles of 64 x 64, without MFMA: 35.7); the
+// 6.5 us with 64 tiles of 32 x 32 (16-k steps on 16 tiles of 64 x 64, without MFMA: 37.2); the
 // forward at T = 512, d = 1024, f = 4096 went 246 -> 78 us.
 // LDS rows are padded by 4 floats: A's [m][k] rows are then read 16 bytes (four k) per lane
 // and B's [k][n] rows 4 bytes per lane without bank conflicts. The MFMA j of a 16-k group
